@@ -177,9 +177,10 @@ typedef struct hda_batch_desc {
 /* Bitmask-allocator replay (Sec. III-B): every heap of `d` must be
  * HDA_BITMAP with arena / align <= max_granules (< 2^32); other heaps get
  * HDA_E_INVAL as status and as every result.  One wavefront per heap keeps
- * one flag per granule and a summary per 4,096 granules (free runs at the
- * bottom, at the top, longest), and searches 64 words of flags or 64
- * summaries per step.  Requests, results, states and statuses as for
+ * the heap's free runs and live blocks in its share of LDS and, once they
+ * outgrow it, one flag per granule and a summary per 4,096 granules (free
+ * runs at the bottom, at the top, longest), searching 64 words of flags or
+ * 64 summaries per step; results are the same on both.  Requests, results, states and statuses as for
  * hda_replay (partial frees included; the live table holds meta_live
  * entries, HDA_E_NOMETA past it; meta_free is not used).  The workspace
  * holds each wave's flags, summaries and live table, about

@@ -1,5 +1,6 @@
 // Bitmask allocator with a next-fit search (Sec. III-B), one wavefront per
-// heap.  The heap's metadata is one flag per granule (set = free), 64 to a
+// heap, for heaps whose free and live tables outgrow the wave's LDS share
+// (hda_bitmap.hip).  The heap's metadata is one flag per granule (set = free), 64 to a
 // word, in device memory, plus the live table the replay driver frees from.
 // An allocation of s granules takes the first s free granules in a row found
 // scanning from the rover (the end of the last allocation), else from granule
@@ -221,6 +222,58 @@ struct BitHeap {
     cn = kNone;
   }
 
+  // Take over a heap from its table of free and live blocks (the lean core's,
+  // whose storage shares this wave's LDS): the live entries go to device
+  // memory, the flags are set block by block (word wi is always written by
+  // lane wi % 64), then summaries and the first live entries go to LDS, which
+  // holds nothing else by then.
+  template <typename Lean>
+  __device__ void take(Lean& t) {
+    const uint32_t lane = lane_id();
+    for (uint32_t base = 0; base < t.L; base += 64u) {
+      const uint32_t i = base + lane;
+      wave_sync();
+      const Ent e = *t.live_ptr(i < t.L ? i : 0u);
+      if (i < t.L) live[i] = e;
+    }
+    for (uint32_t w0 = 0; w0 < nw; w0 += 64u)
+      if (w0 + lane < nw) bits[w0 + lane] = 0ull;
+    for (uint32_t j = 0; j < t.F; ++j) {
+      uint32_t a, s, k;
+      t.read(j, a, s, k);
+      const uint32_t last = (a + s - 1u) >> 6;
+      for (uint32_t n = a >> 12; n <= (last >> 6); ++n) {
+        const uint32_t wi = 64u * n + lane;
+        const uint64_t m = word_mask(wi, a, s);
+        const uint64_t v = load(wi) | m;
+        if (m != 0ull) bits[wi] = v;
+      }
+    }
+    for (uint32_t n = 0; n < nn; ++n) put_node(n, node_summary(load(64u * n + lane)));
+    for (uint32_t base = 0; base < t.L && base < kl; base += 64u) {
+      const uint32_t i = base + lane;
+      wave_sync();
+      if (i < t.L && i < kl) llive[i] = live[i];
+    }
+    wave_sync();
+    L = t.L;
+    rover = t.rover;
+    cn = kNone;
+  }
+
+  // The bits of word wi inside [p, p + s) (s >= 1).  32-bit: 64 wi and p + s
+  // stay below 2^32; for a word in the range lo is 0..63 and e at least 1,
+  // and other words are masked off.
+  __device__ __forceinline__ static uint64_t word_mask(uint32_t wi, uint32_t p, uint32_t s) {
+    const bool in = wi >= (p >> 6) && wi <= ((p + s - 1u) >> 6);
+    const uint32_t b0 = 64u * wi;
+    const uint32_t lo = p > b0 ? p - b0 : 0u;
+    const uint32_t e = p + s - b0;
+    const uint32_t hi = e < 64u ? e : 64u;
+    return in ? (hi == 64u ? ~0ull : (1ull << (hi & 63u)) - 1ull) & ~((1ull << (lo & 63u)) - 1ull)
+              : 0ull;
+  }
+
   // One step over node n's 64 words: the lowest p >= lo whose s-th granule
   // p + s - 1 lies in the node, with `carry` free granules in a row ending
   // just below the node (granules below lo count as used), or kNone; carry
@@ -321,14 +374,7 @@ struct BitHeap {
     for (uint32_t n = p >> 12; n <= (last >> 6); ++n) {
       const uint32_t wi = 64u * n + lane_id();
       const bool in = wi >= first && wi <= last;
-      // 32-bit: 64 wi and p + s stay below 2^32; for a word in the range
-      // lo is 0..63 and e at least 1, and other words are masked off below
-      const uint32_t b0 = 64u * wi;
-      const uint32_t lo = p > b0 ? p - b0 : 0u;
-      const uint32_t e = p + s - b0;
-      const uint32_t hi = e < 64u ? e : 64u;
-      const uint64_t m = in ? (hi == 64u ? ~0ull : (1ull << hi) - 1ull) & ~((1ull << (lo & 63u)) - 1ull)
-                            : 0ull;
+      const uint64_t m = word_mask(wi, p, s);
       uint64_t v;
       if (n == cn)
         v = cw;

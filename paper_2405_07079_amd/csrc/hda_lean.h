@@ -83,6 +83,7 @@ struct __attribute__((aligned(16))) SegRec {
 template <int ALGO, int RF>
 struct LeanHeap {
   static constexpr bool kSeg = ALGO == kSegFit || ALGO == kTlsf;
+  static constexpr bool kRover = ALGO == kNextFit || ALGO == kBitmap;
   static constexpr uint32_t kKeyShift = SegKey<ALGO>::kShift;
   static constexpr uint32_t kStampLimit = SegKey<ALGO>::kLimit;
   static constexpr uint32_t kStampMask = SegKey<ALGO>::kMask;
@@ -95,6 +96,7 @@ struct LeanHeap {
   int64_t arena;
   uint32_t shift, ag;
   uint32_t F, L, rover, clock;
+  uint32_t hint;                  // kBitmap: the entry the last allocation cut (may be stale)
   uint32_t capF, capL;            // the caller's capacities (E_NOMETA past them)
   uint32_t live_room;             // live entries the pool holds beside the current free chunks
 
@@ -259,7 +261,7 @@ struct LeanHeap {
   __device__ __forceinline__ void init() {
 #pragma unroll
     for (int k = 0; k < RF; ++k) { fa[k] = kNone; fs[k] = 0u; fk[k] = kNone; }
-    F = 1; L = 0; rover = 0; clock = 1;
+    F = 1; L = 0; rover = 0; clock = 1; hint = 0;
     set_room();
     write(0, 0u, ag, kSeg ? seg_key(ag) : 0u);
   }
@@ -277,6 +279,73 @@ struct LeanHeap {
     clear(last);
     F = last;
     if (CHK) set_room();
+  }
+
+  // Append a free entry (the caller has checked the pool and the capacity).
+  template <bool CHK = true>
+  __device__ __forceinline__ void append(uint32_t a, uint32_t s, uint32_t k) {
+    if (F >= HF && ((F - HF) & 63u) == 0u) {  // a new LDS chunk: its slots start empty
+      wave_sync();
+      cold_put(F - HF + lane_id(), kNone, 0u, kNone);
+    }
+    write(F, a, s, k);
+    ++F;
+    if (CHK) set_room();
+  }
+
+  // Bitmask allocator (Sec. III-B, one flag per granule, searched from the
+  // rover): the free runs of the flags are exactly the free blocks, so its
+  // answers follow from the table.  The run taken starts at the lowest
+  // p >= rover with sg free granules in a row -- max(address, rover) of some
+  // block -- else at the lowest address of a block that fits.  p is the first
+  // granule taken, (a, s) the block it lies in.
+  //
+  // The block that holds the rover comes first in that order, and after an
+  // allocation it is the remainder the last one left, so its entry is tried
+  // before the scan: at 16 MiB heaps of 64 B granules most allocations end
+  // there.  An entry that moved meanwhile fails the test below (free blocks
+  // do not overlap: a block holding the rover is the one that does) and the
+  // scan decides.
+  __device__ __forceinline__ bool select_run(uint32_t sg, uint32_t& j, uint32_t& a, uint32_t& s,
+                                             uint32_t& p) {
+    if (hint < F) {
+      read_block(hint, a, s);
+      const uint32_t below = rover - a;  // < s exactly when the block holds the rover
+      if (below < s && s - below >= sg) {
+        j = hint;
+        p = rover;
+        return true;
+      }
+    }
+    uint32_t best = kNone, bc = 0;
+    scan([&](uint32_t c, uint32_t ea, uint32_t es, uint32_t) {
+      const uint32_t end = ea + es, st = ea > rover ? ea : rover;
+      const uint32_t past = end > st ? end - st : 0u;  // granules from the rover on
+      const uint32_t t = es >= sg ? (past >= sg ? st : ea) - rover : kNone;
+      const bool lt = t < best;
+      best = lt ? t : best;
+      bc = lt ? c : bc;
+    });
+    const uint32_t K = wave_min(best);
+    uint64_t mk;
+    if (K != kNone) {
+      mk = ballot(best == K);
+    } else {
+      // a block starting right below the rover has key ~0 as well
+      uint64_t any = 0ull;
+      scan([&](uint32_t c, uint32_t ea, uint32_t es, uint32_t) {
+        const bool hit = es >= sg && ea + 1u == rover;
+        any |= ballot(hit);
+        bc = hit ? c : bc;
+      });
+      if (any == 0ull) return false;
+      mk = any;
+    }
+    const uint32_t l = ctz64(mk);
+    j = 64u * rdlane(bc, l) + l;
+    p = K + rover;
+    read_block(j, a, s);
+    return true;
   }
 
   // Selection.  On success j is the chosen entry and (a, s) its block.
@@ -385,6 +454,30 @@ struct LeanHeap {
   template <bool CHK = true>
   __device__ __forceinline__ int64_t alloc(uint32_t sg, uint32_t kreq) {
     uint32_t j = 0, a = 0, s = 0;
+    if constexpr (ALGO == kBitmap) {
+      uint32_t p = 0;
+      if (!select_run(sg, j, a, s, p)) return kFail;
+      if (CHK && L >= capL) return kENoMeta;
+      if (CHK && L >= live_room) return kOverflow;
+      // the part below p stays, the part above the run is the new remainder
+      const uint32_t below = p - a, above = s - below - sg;
+      hint = j;
+      if (below == 0u) {
+        if (above != 0u) write(j, p + sg, above, 0u);
+        else remove<CHK>(j);
+      } else {
+        if (above != 0u) {
+          if (CHK && need_bytes(F + 1u, L + 1u) > m.bytes) return kOverflow;
+          hint = F;
+          append<CHK>(p + sg, above, 0u);
+        }
+        write(j, a, below, 0u);
+      }
+      live_write(L, p, sg);
+      ++L;
+      rover = p + sg;
+      return (int64_t)((uint64_t)p << shift);
+    }
     if (!select(sg, kreq, j, a, s)) return kFail;
     if (CHK && L >= capL) return kENoMeta;
     if (CHK && L >= live_room) return kOverflow;
@@ -434,13 +527,7 @@ struct LeanHeap {
       if (CHK && F >= capF) return kENoMeta;
       // (the freed block still counts as live here: the check is on the safe side)
       if (CHK && need_bytes(F + 1u, L) > m.bytes) return kOverflow;
-      if (F >= HF && ((F - HF) & 63u) == 0u) {  // a new LDS chunk: its slots start empty
-        wave_sync();
-        cold_put(F - HF + lane_id(), kNone, 0u, kNone);
-      }
-      write(F, x, sz, kSeg ? seg_key(sz) : 0u);
-      ++F;
-      if (CHK) set_room();
+      append<CHK>(x, sz, kSeg ? seg_key(sz) : 0u);
     } else if (MR == 0ull) {
       const uint32_t l = ctz64(ML), jl = 64u * (rdlane(cl, l) - 1u) + l;
       const uint32_t sl = size_at(jl);
@@ -580,7 +667,7 @@ struct LeanHeap {
       }
     }
     if (lane == 0) {
-      tail[0] = ALGO == kNextFit ? (int64_t)((uint64_t)rover << sh) : -1;
+      tail[0] = kRover ? (int64_t)((uint64_t)rover << sh) : -1;
       tail[1] = kSeg ? (int64_t)bm : 0;
     }
     if constexpr (ALGO == kTlsf) {

@@ -11,6 +11,8 @@
 
 namespace hda {
 
+constexpr int kBitmapRF = 2;  // free-table chunks in registers (bitmask allocator)
+
 struct ReplayParams {
   const int64_t* arena;
   const int64_t* align;
@@ -325,6 +327,36 @@ __device__ __forceinline__ void ord_any_heap(const ReplayParams& p, HDA_LDS uint
     case kTlsf: ord_replay_heap<kTlsf>(p, pool, dev, h, heap); break;
     default: reject_heap(p, heap); break;  // the bitmask allocator has its own kernel
   }
+}
+
+// Bitmask-allocator replay of one heap from its table of free blocks in the
+// wave's LDS pool; a heap whose tables outgrow the pool continues on the
+// flags (hda_bitmap.h) in the wave's workspace slot, the first kn summaries
+// and kl live entries in the same LDS.
+__device__ __forceinline__ void bitmap_lean_heap(const ReplayParams& p, const LeanLds& lds,
+                                                 uint64_t* bits, uint64_t* nodes, Ent* live,
+                                                 uint32_t kn, uint64_t max_granules,
+                                                 int64_t heap) {
+  HeapRegs h;
+  if (!heap_params(p, heap, h) || h.algo != kBitmap || (uint64_t)h.ag > max_granules) {
+    reject_heap(p, heap);
+    return;
+  }
+  LeanHeap<kBitmap, kBitmapRF> w(lds, h, kNone, p.cap_live);
+  w.init();
+  int32_t st = 0;
+  const int64_t b1 = p.req_off[heap + 1];
+  const int64_t pos = run_requests<kBitmap>(p, w, p.req_off[heap], b1, h.shift, h.arena, st);
+  if (pos == b1) {
+    finish_heap(p, w, heap, st);
+    return;
+  }
+  BitHeap b(bits, nodes, live, (HDA_LDS uint64_t*)lds.base, kn,
+            (HDA_LDS Ent*)(lds.base + 8u * kn), (lds.bytes - 8u * kn) / 8u, h, p.cap_live);
+  b.take(w);
+  if (lane_id() == 0 && p.migrated) atomicAdd(p.migrated, 1u);
+  run_requests<kBitmap>(p, b, pos, b1, h.shift, h.arena, st);
+  finish_heap(p, b, heap, st);
 }
 
 // Bitmask-allocator replay of one heap (hda_bitmap.h) in a workspace slot
