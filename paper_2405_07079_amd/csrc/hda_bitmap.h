@@ -142,6 +142,7 @@ __device__ __forceinline__ uint32_t node_ends(uint64_t w) {
 typedef uint32_t __attribute__((may_alias)) sum_half_t;
 
 struct BitHeap {
+  static constexpr bool kGranules = true;  // alloc / free_draw return granules
   HDA_GLOBAL uint64_t* bits;   // nw words: bit i of word w = granule 64 w + i free
   HDA_GLOBAL uint64_t* nodes;  // nn node summaries, node n = words 64 n .. 64 n + 63
   HDA_GLOBAL Ent* live;        // capL entries
@@ -239,9 +240,9 @@ struct BitHeap {
     for (uint32_t w0 = 0; w0 < nw; w0 += 64u)
       if (w0 + lane < nw) bits[w0 + lane] = 0ull;
     for (uint32_t j = 0; j < t.F; ++j) {
-      uint32_t a, s, k;
-      t.read(j, a, s, k);
-      const uint32_t last = (a + s - 1u) >> 6;
+      uint32_t a, e, k;
+      t.read(j, a, e, k);
+      const uint32_t s = e - a, last = (e - 1u) >> 6;
       for (uint32_t n = a >> 12; n <= (last >> 6); ++n) {
         const uint32_t wi = 64u * n + lane;
         const uint64_t m = word_mask(wi, a, s);
@@ -391,7 +392,7 @@ struct BitHeap {
     }
   }
 
-  // Allocate sg granules (sg >= 1).  Returns the byte offset, -1 or kENoMeta.
+  // Allocate sg granules (sg >= 1).  Returns the first granule, -1 or kENoMeta.
   // (CHK: no request of this core ends its run, so there is nothing to check)
   template <bool CHK = true>
   __device__ int64_t alloc(uint32_t sg, uint32_t) {
@@ -405,12 +406,12 @@ struct BitHeap {
     live_put(L, mk_ent(p, sg));
     ++L;
     rover = p + sg;
-    return (int64_t)((uint64_t)p << shift);
+    return (int64_t)(uint64_t)p;
   }
 
   // Replay free: the victim is live[(r * L) >> 32]; it keeps its first
   // floor(cut * size / 2^31) granules (partial deallocation); nothing live
-  // -> -1.  Returns the byte offset of the freed part.
+  // -> -1.  Returns the first granule of the freed part.
   template <bool CHK = true>
   __device__ int64_t free_draw(uint32_t r, uint32_t cut) {
     if (L == 0u) return kFail;
@@ -427,12 +428,8 @@ struct BitHeap {
       live_put(idx, mk_ent(uniform(ent_a(last)), uniform(ent_s(last))));
       --L;
     }
-    return (int64_t)((uint64_t)(x + t) << shift);
+    return (int64_t)(uint64_t)(x + t);
   }
-
-  // Every block may run without the run-ending checks of the other cores.
-  __device__ __forceinline__ bool block_safe(uint32_t) const { return true; }
-  __device__ __forceinline__ void set_room() {}
 
   // Canonical state (format in hda.h): the free runs in address order, the
   // live table, the rover.

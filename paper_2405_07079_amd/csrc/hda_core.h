@@ -192,6 +192,7 @@ struct WaveHeap {
   // per-class counts (TLSF's 2,048 classes are found by a reduction instead)
   static constexpr bool kSeg = ALGO == kSegFit || ALGO == kTlsf;
   static constexpr bool kCounts = ALGO == kSegFit;
+  static constexpr bool kGranules = false;  // alloc / free_draw return bytes
 
   Cold c;
   HeapRegs h;

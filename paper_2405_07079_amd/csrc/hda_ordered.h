@@ -509,6 +509,7 @@ struct OrdHeap {
   using TA = Hal<false, kMax, D>;
   using TB = Hal<true, false, D>;
   using Row = typename TA::Row;
+  static constexpr bool kGranules = true;  // alloc / free_draw return granules
 
   TA ta;
   TB tb;
@@ -710,11 +711,11 @@ struct OrdHeap {
     lset(L, mk_ent(a, sg));
     ++L;
     if (ALGO == kNextFit) rover = a + sg;
-    return (int64_t)((uint64_t)a << shift);
+    return (int64_t)(uint64_t)a;
   }
 
   // Allocate sg granules; kreq is the request's byte class (segregated fit)
-  // or request class (TLSF).  Returns the byte offset, -1 or kENoMeta.
+  // or request class (TLSF).  Returns the first granule, -1 or kENoMeta.
   __device__ __forceinline__ bool full_dir() const {
     return D < kOrdDir && (ta.nc >= 64u * D || (kKeys && tb.nc >= 64u * D));
   }
@@ -839,7 +840,7 @@ struct OrdHeap {
       }
       lset(L, mk_ent(b.a, sg));
       ++L;
-      return (int64_t)((uint64_t)b.a << shift);
+      return (int64_t)(uint64_t)b.a;
     }
   }
 
@@ -952,8 +953,8 @@ struct OrdHeap {
   }
 
   // Free live entry idx except its first floor(cut * size / 2^31) granules
-  // (partial deallocation, sequential fits; cut < 2^31).  Returns the byte
-  // offset of the released part or kENoMeta.
+  // (partial deallocation, sequential fits; cut < 2^31).  Returns the first
+  // granule of the released part or kENoMeta.
   template <bool CHK = true>
   __device__ __forceinline__ int64_t free_index(uint32_t idx, uint32_t cut) {
     if (CHK && full_dir()) return kOverflow;
@@ -973,7 +974,7 @@ struct OrdHeap {
       lset(idx, w);
       L = last;
     }
-    return (int64_t)((uint64_t)x << shift);
+    return (int64_t)(uint64_t)x;
   }
 
   template <bool CHK = true>

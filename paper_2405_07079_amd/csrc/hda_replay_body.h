@@ -80,32 +80,31 @@ template <int A, int D>
 struct UncheckedBlocks<OrdHeap<A, D>> {
   static constexpr bool value = true;
 };
-template <>
-struct UncheckedBlocks<BitHeap> {
-  static constexpr bool value = true;
-};
 
 // Requests j < n of one block of 64 on core w: lane j of w0 holds request
 // j's draw (free) or size in granules (allocation, 0 = larger than the
 // arena), lane j of w1 its byte class (segregated fit) or its cut (free,
-// other fits; read only when CUT), bit j of mfree marks the frees.  Results
-// go to lane j of olo / ohi.  Returns the number of requests run: n, or the
+// other fits; read only when CUT), bit j of mfree marks the frees.  Lane j of
+// `out` receives the result.  Returns the number of requests run: n, or the
 // index of the request that found the lean core's tiers too small.  UNCHK:
 // the core's block_safe holds for the block, so no request can find the
-// tiers (or the ordered core's directory) too small and the checks are
-// compiled out.
+// tiers (or the ordered core's directory) too small, and no request of the
+// block is larger than the arena, so those checks are compiled out; the only
+// failure is then "nothing fits", and a result is one register per lane (the
+// granule, or kNone, which no block starts at).
 template <int ALGO, bool CUT, bool UNCHK, typename Core>
 __device__ __forceinline__ uint32_t run_block(Core& w, uint32_t n, uint32_t w0, uint32_t w1,
-                                              uint64_t mfree, uint32_t& olo, uint32_t& ohi,
+                                              uint64_t mfree, uint32_t shift, int64_t& out,
                                               int32_t& st) {
-  uint32_t done = n;
-  for (uint32_t j = 0; j < n; ++j) {
+  uint32_t done = n, olo = 0, ohi = 0;
+  uint64_t frees = mfree;  // bit 0: the current request
+  for (uint32_t j = 0; j < n; ++j, frees >>= 1) {
     const uint32_t v0 = rdlane(w0, j);
     int64_t r;
-    if ((mfree >> j) & 1ull) {
+    if (keep_scalar((uint32_t)frees) & 1u) {
       if constexpr (UNCHK) r = w.template free_draw<false>(v0, CUT ? rdlane(w1, j) : 0u);
       else r = w.free_draw(v0, CUT ? rdlane(w1, j) : 0u);
-    } else if (v0 == 0u) {
+    } else if (!UNCHK && v0 == 0u) {
       r = kFail;
     } else {
       if constexpr (UNCHK) r = w.template alloc<false>(v0, seg_like(ALGO) ? rdlane(w1, j) : 0u);
@@ -113,13 +112,18 @@ __device__ __forceinline__ uint32_t run_block(Core& w, uint32_t n, uint32_t w0, 
     }
     if (!UNCHK && r == kOverflow) { done = j; break; }
     olo = put_lane(olo, j, (uint32_t)(uint64_t)r);
-    ohi = put_lane(ohi, j, (uint32_t)((uint64_t)r >> 32));
+    if constexpr (!UNCHK) ohi = put_lane(ohi, j, (uint32_t)((uint64_t)r >> 32));
   }
-  // the heap's status: its first capacity error, looked for once per block
-  // rather than once per request
-  const bool nometa = lane_id() < done && olo == (uint32_t)(uint64_t)kENoMeta &&
-                      ohi == (uint32_t)((uint64_t)kENoMeta >> 32);
-  if (st == 0 && ballot(nometa) != 0ull) st = (int32_t)kENoMeta;
+  if constexpr (UNCHK) {
+    static_assert(Core::kGranules, "a granule fits one register");
+    out = olo == kNone ? kFail : (int64_t)((uint64_t)olo << shift);
+  } else {
+    const int64_t r = (int64_t)(((uint64_t)ohi << 32) | olo);
+    out = Core::kGranules && r >= 0 ? (int64_t)((uint64_t)r << shift) : r;
+    // the heap's status: its first capacity error, looked for once per block
+    // rather than once per request
+    if (st == 0 && ballot(lane_id() < done && r == kENoMeta) != 0ull) st = (int32_t)kENoMeta;
+  }
   return done;
 }
 
@@ -155,36 +159,35 @@ __device__ __forceinline__ int64_t run_requests(const ReplayParams& p, Core& w, 
                                         : (is_free ? (uint32_t)(~(uint64_t)q >> 32) : 0u);
     const uint64_t mfree = ballot(is_free);
     const uint32_t n = (uint32_t)min<int64_t>(64, to - base);
-    uint32_t olo = 0, ohi = 0;
+    int64_t out = 0;
     // a block whose frees carry no cut runs a copy with the partial-free
-    // logic folded away; on the lean and ordered cores, such a block that
-    // cannot outgrow the tiers (the directory) also runs without the checks
+    // logic folded away; such a block, and one with cuts, that cannot outgrow
+    // the tiers (the directory) also runs without the checks (a partial free
+    // adds at most one free entry and keeps its live entry, so the block test
+    // holds for it too)
     const bool cut = !seg_like(ALGO) && ballot(is_free && w1 != 0u) != 0ull;
-    uint32_t done;
+    bool safe = false;
+    if constexpr (UncheckedBlocks<Core>::value)
+      safe = w.block_safe(n) && ballot(!is_free && w0 == 0u) == 0ull;
+    uint32_t done = 0;
     if (cut) {
-      // (a partial free adds at most one free entry and keeps its live
-      // entry, so the block test holds for these blocks too)
-      if constexpr (UncheckedBlocks<Core>::value) {
-        if (w.block_safe(n)) {
-          done = run_block<ALGO, !seg_like(ALGO), true>(w, n, w0, w1, mfree, olo, ohi, st);
+      if (safe) {
+        if constexpr (UncheckedBlocks<Core>::value) {
+          done = run_block<ALGO, !seg_like(ALGO), true>(w, n, w0, w1, mfree, shift, out, st);
           w.set_room();
-        } else {
-          done = run_block<ALGO, !seg_like(ALGO), false>(w, n, w0, w1, mfree, olo, ohi, st);
         }
       } else {
-        done = run_block<ALGO, !seg_like(ALGO), false>(w, n, w0, w1, mfree, olo, ohi, st);
+        done = run_block<ALGO, !seg_like(ALGO), false>(w, n, w0, w1, mfree, shift, out, st);
       }
-    } else if constexpr (UncheckedBlocks<Core>::value) {
-      if (w.block_safe(n)) {
-        done = run_block<ALGO, false, true>(w, n, w0, w1, mfree, olo, ohi, st);
+    } else if (safe) {
+      if constexpr (UncheckedBlocks<Core>::value) {
+        done = run_block<ALGO, false, true>(w, n, w0, w1, mfree, shift, out, st);
         w.set_room();
-      } else {
-        done = run_block<ALGO, false, false>(w, n, w0, w1, mfree, olo, ohi, st);
       }
     } else {
-      done = run_block<ALGO, false, false>(w, n, w0, w1, mfree, olo, ohi, st);
+      done = run_block<ALGO, false, false>(w, n, w0, w1, mfree, shift, out, st);
     }
-    if (lane < done) p.res[base + lane] = (int64_t)(((uint64_t)ohi << 32) | olo);
+    if (lane < done) p.res[base + lane] = out;
     if (done < n) return base + done;
   }
   return to;
