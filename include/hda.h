@@ -127,9 +127,10 @@ int hda_set_device_allocator(hda_dev_alloc_fn alloc, hda_dev_free_fn release, vo
  * one LDS pool per heap of lds_free * 16 + lds_live * 8 bytes (defaults 128
  * and 1024: 10 KiB), free entries from its start and live entries from its
  * end.  A heap whose tables outgrow the pool before reaching meta_free /
- * meta_live moves them, mid-trace, to the general path in its device-memory
- * slot of the workspace and continues there; results do not depend on the
- * tuning.  reg_free = -1 selects the general path for every heap: no
+ * meta_live moves them, mid-trace, to the ordered core (pools of 10 KiB or
+ * more, meta_free up to 4,096, and a workspace that holds its slots; else to
+ * the general path) in its device-memory slot of the workspace and continues
+ * there; results do not depend on the tuning.  reg_free = -1 selects the general path for every heap: no
  * registers, lds_free free and lds_live live entries in LDS (defaults 64 and
  * 1024), the rest in device memory (workspace).  reg_live must be 0 or -1
  * (the live table is never held in registers).  0 = default for every
@@ -190,8 +191,10 @@ typedef struct hda_batch_desc {
 size_t hda_bitmap_workspace(const hda_batch_desc *d, uint64_t max_granules);
 int hda_bitmap_replay(const hda_batch_desc *d, uint64_t max_granules, void *stream);
 
-/* Bytes of device scratch hda_replay needs for `d` (reads only n_heaps,
- * meta_free, meta_live and tuning).  Returns 0 on invalid arguments. */
+/* Bytes of device scratch for hda_replay on `d` (reads only n_heaps,
+ * meta_free, meta_live and tuning).  A smaller workspace is taken as long as
+ * it holds the general path's slots (12 instead of 32 bytes per free entry of
+ * capacity and heap in flight).  Returns 0 on invalid arguments. */
 size_t hda_replay_workspace(const hda_batch_desc *d);
 
 /* hda_replay for callers that cannot allocate device memory (code under

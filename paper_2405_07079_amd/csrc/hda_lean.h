@@ -25,10 +25,10 @@
 // heap of 64 KiB from 272 to 224 ns a request.
 //
 // When the tables would outgrow the pool before reaching the capacities the
-// caller asked for, the request stops with kOverflow (changing nothing), the
-// tables move into the general core's layout (hda_core.h, whose tables
-// continue into device memory) and the heap goes on there.  Results are the
-// same on both paths.
+// caller asked for, the request stops with kOverflow (changing nothing) and
+// the heap goes on with its tables in the ordered core (hda_ordered.h) or in
+// the general core (hda_core.h), both of which continue into device memory.
+// Results are the same on every path.
 //
 // Same rules as the general core: values that feed a cross-lane operation are
 // never produced under a lane-dependent branch, and every LDS access is
@@ -267,7 +267,7 @@ struct LeanHeap {
   // LDS chunks, where most scans end, are at fixed places; later ones are
   // loaded four at a time before any is used, so their latencies overlap.
   template <int N, typename Fn>
-  __device__ __forceinline__ void scan_cold(uint32_t c, Fn&& f) {
+  __device__ __forceinline__ void scan_cold(uint32_t c, Fn&& f) const {
     wave_sync();
     uint32_t ea[N], ee[N], ek[N];
 #pragma unroll
@@ -288,6 +288,15 @@ struct LeanHeap {
     uint32_t c = RF + 2;
     for (; 64u * (c + 3u) < F; c += 4u) scan_cold<4>(c, f);
     for (; 64u * c < F; ++c) scan_cold<1>(c, f);
+  }
+
+  // The same one chunk at a time, for work done once per heap (one copy of f
+  // for the LDS chunks).
+  template <typename Fn>
+  __device__ __forceinline__ void each_chunk(Fn&& f) const {
+#pragma unroll
+    for (int k = 0; k < RF; ++k) f((uint32_t)k, fa[k], fe[k], kSeg ? fk[k] : 0u);
+    for (uint32_t c = RF; 64u * c < F; ++c) scan_cold<1>(c, f);
   }
 
   // Alg. 6: one free block [0, A).

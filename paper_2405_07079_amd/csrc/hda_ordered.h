@@ -74,6 +74,14 @@ __device__ __forceinline__ uint64_t lanes_below(uint32_t n) {
   return n >= 64u ? ~0ull : (1ull << n) - 1ull;
 }
 
+// Memory accesses before this point are not moved past it by the compiler
+// (the hardware keeps a wave's accesses in order): for data that one lane
+// writes and another reads.
+__device__ __forceinline__ void wave_order() {
+  wave_sync();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // Directory access: lane (i & 63) of register i >> 6.
 template <int D>
 __device__ __forceinline__ uint32_t dir_get(const uint32_t (&v)[D], uint32_t i) {
@@ -460,11 +468,31 @@ __host__ __device__ constexpr uint64_t ord_dev_bytes(uint32_t cap_live) {
   return kOrdTableBytes + kOrdSecondBytes + (uint64_t)cap_live * 8u;
 }
 
+// A heap that starts on the lean core and moves here (OrdHeap::adopt) has a
+// device slot cut to its capacity: chunks hold at least 32 entries, so
+// cap_free entries (a multiple of 64) take at most cap_free / 32 chunk slots,
+// 16 bytes an entry, and its records or key table the same.
+__host__ __device__ constexpr uint64_t ord_area_bytes(uint32_t cap_free) {
+  return (uint64_t)cap_free * 16u;
+}
+__host__ __device__ constexpr uint64_t ord_spill_bytes(uint32_t cap_free, uint32_t cap_live) {
+  return 2u * ord_area_bytes(cap_free) + (uint64_t)cap_live * 8u;
+}
+// Free blocks such a heap may bring: adopt() stages them beside the chunks
+// (9.2 bytes an entry) and beside the records (16) it builds from them.
+__host__ __device__ constexpr uint32_t ord_adopt_max(uint32_t cap_free) {
+  return cap_free - cap_free / 4u;
+}
+// The least pool for it: TLSF's list heads are always in LDS.
+constexpr uint32_t kOrdMinPool = kOrdTlsfHeadBytes + 2048u;
+
 // Split a wave's pool (`pool_bytes`, of which `slot_bytes` are meant for the
-// tables and records) and its device slot for an algorithm.
+// tables and records) and its device slot, whose two table areas take
+// `area_bytes` each, for an algorithm.
 __device__ __forceinline__ OrdMem ord_mem(int algo, HDA_LDS uint8_t* pool, uint32_t pool_bytes,
                                           uint32_t slot_bytes, HDA_GLOBAL uint8_t* dev,
-                                          uint32_t cap_live) {
+                                          uint32_t cap_live,
+                                          uint32_t area_bytes = (uint32_t)kOrdTableBytes) {
   OrdMem m;
   uint32_t off = 0;
   m.heads = (HDA_LDS uint32_t*)pool;
@@ -489,12 +517,13 @@ __device__ __forceinline__ OrdMem ord_mem(int algo, HDA_LDS uint8_t* pool, uint3
   m.rec_n = nr;
   off += nr * 16u;
   m.ta_g = dev;
-  m.tb_g = dev + kOrdTableBytes;
-  m.rec_g = (HDA_GLOBAL u32x4*)(dev + kOrdTableBytes);
+  m.tb_g = dev + area_bytes;
+  m.rec_g = (HDA_GLOBAL u32x4*)(dev + area_bytes);
   m.ll = (HDA_LDS Ent*)(pool + off);
-  const uint32_t nl = pool_bytes > off ? (pool_bytes - off) / 8u : 0u;
+  // whole 64-entry chunks, so that each lies on one side
+  const uint32_t nl = pool_bytes > off ? ((pool_bytes - off) / 8u) & ~63u : 0u;
   m.ll_n = nl < cap_live ? nl : cap_live;
-  m.gl = (HDA_GLOBAL Ent*)(dev + kOrdTableBytes + kOrdSecondBytes);
+  m.gl = (HDA_GLOBAL Ent*)(dev + 2u * (uint64_t)area_bytes);
   return m;
 }
 
@@ -718,6 +747,163 @@ struct OrdHeap {
   // or request class (TLSF).  Returns the first granule, -1 or kENoMeta.
   __device__ __forceinline__ bool full_dir() const {
     return D < kOrdDir && (ta.nc >= 64u * D || (kKeys && tb.nc >= 64u * D));
+  }
+
+  // Where a heap that comes from the lean core leaves its free entries
+  // (address, end) and their keys: the tops of the two table areas.
+  __device__ __forceinline__ HDA_GLOBAL Ent* staged_ents(uint32_t f) const {
+    return (HDA_GLOBAL Ent*)(m.tb_g - (uint64_t)f * 8u);
+  }
+  __device__ __forceinline__ HDA_GLOBAL uint32_t* staged_keys(uint32_t f) const {
+    return (HDA_GLOBAL uint32_t*)(m.tb_g + (m.tb_g - m.ta_g) - (uint64_t)f * 4u);
+  }
+  // Write lean heap w's live entries and free entries (in table order) to
+  // the device slot: its tables share the LDS this core is about to use.
+  template <typename Lean>
+  __device__ __forceinline__ void stage(const Lean& w) const {
+    const uint32_t lane = lane_id();
+    for (uint32_t base = 0; base < w.L; base += 64u) {
+      const uint32_t i = base + lane;
+      wave_sync();
+      const Ent e = *w.live_ptr(i < w.L ? i : 0u);
+      if (i < w.L) m.gl[i] = e;
+    }
+    HDA_GLOBAL Ent* const ents = staged_ents(w.F);
+    HDA_GLOBAL uint32_t* const keys = staged_keys(w.F);
+    w.each_chunk([&](uint32_t c, uint32_t a, uint32_t e, uint32_t k) {
+      const uint32_t i = 64u * c + lane;
+      if (i < w.F) {
+        ents[i] = mk_ent(a, e);
+        if (kSeg) keys[i] = k;
+      }
+    });
+    wave_order();
+  }
+  // Start from f staged free entries and l staged live entries: each lane
+  // finds the place of its entries in the sorted tables by counting the
+  // entries below them (f^2 / 64 steps, about 0.1 ms at 500 free blocks,
+  // once), and the chunks, records and first live entries go where this core
+  // keeps them.  At most ord_adopt_max(capF) free blocks; chunk i is slot i.
+  // kshift: the position of the class in a key.
+  __device__ __forceinline__ void adopt(uint32_t f, uint32_t l0, uint32_t rov, uint32_t kshift) {
+    const uint32_t lane = lane_id();
+    F = f; L = l0; rover = rov;
+    HDA_GLOBAL Ent* const ents = staged_ents(F);
+    HDA_GLOBAL uint32_t* const keys = staged_keys(F);
+    ta.init(m.ta_l, m.ta_g, m.ta_n);
+    if constexpr (kKeys) tb.init(m.tb_l, m.tb_g, m.tb_n);
+    // chunk i takes entries [i F / n, (i + 1) F / n): 32 to 64 of them each
+    // when there are two or more
+    const uint32_t n = F <= 64u ? 1u : (F + 55u) / 56u;
+    for (uint32_t base = 0; base < F; base += 64u) {
+      const uint32_t i = base + lane;
+      const bool v = i < F;
+      const uint32_t iv = v ? i : 0u;
+      wave_sync();
+      const Ent me = ents[iv];
+      const uint32_t a = ent_a(me), e = ent_s(me), s = e - a, k = kSeg ? keys[iv] : 0u;
+      // entries below this one by end; by (size, end) or by key
+      uint32_t ra = 0, rb = 0;
+      bool newer = false, older = false;  // in the same class list
+      for (uint32_t d = 0; d < F; d += 64u) {
+        const uint32_t t = d + lane < F ? d + lane : 0u;
+        wave_sync();
+        const Ent o = ents[t];
+        const uint32_t ko = kSeg ? keys[t] : 0u;
+        const uint32_t m1 = F - d < 64u ? F - d : 64u;
+        for (uint32_t l = 0; l < m1; ++l) {
+          const uint32_t ej = rdlane(ent_s(o), l);
+          ra += ej < e ? 1u : 0u;
+          if constexpr (kKeys) {
+            const uint32_t sj = ej - rdlane(ent_a(o), l);
+            rb += (sj < s || (sj == s && ej < e)) ? 1u : 0u;
+          }
+          if constexpr (kSeg) {
+            const uint32_t kj = rdlane(ko, l);
+            const bool list = (kj >> kshift) == (k >> kshift);
+            rb += kj < k ? 1u : 0u;
+            newer = newer || (list && kj < k);
+            older = older || (list && kj > k);
+          }
+        }
+      }
+      if (v) {
+        // a record's number is its rank by key: a class's blocks are
+        // numbered one after another from the head
+        place(m.ta_g, ra, n, e, kSeg ? rb : s);
+        if constexpr (kKeys) place(m.tb_g, rb, n, e, s);
+        if constexpr (kSeg) {
+          u32x4 r;
+          r[0] = a; r[1] = s;
+          r[2] = older ? rb + 1u : kNone;
+          r[3] = newer ? rb - 1u : kNone;
+          m.rec_g[rb] = r;
+        }
+      }
+    }
+    wave_order();
+    build(ta, n);
+    if constexpr (kKeys) build(tb, n);
+    hd = kNone; bm = 0ull; slb = 0u; frl = frh = 0u;
+    if constexpr (kSeg) {
+      // free record numbers: F .. capF - 1
+      const uint32_t b0 = 64u * lane;
+      const uint64_t fr = lanes_below(capF > b0 ? capF - b0 : 0u) &
+                          ~lanes_below(F > b0 ? F - b0 : 0u);
+      frl = (uint32_t)fr;
+      frh = (uint32_t)(fr >> 32);
+      if constexpr (ALGO == kTlsf) {
+        for (uint32_t c = 0; c < kTlsfClasses; c += 64u) {
+          wave_sync();
+          m.heads[c + lane] = kNone;
+        }
+      }
+      for (uint32_t base = 0; base < F; base += 64u) {
+        const uint32_t i = base + lane;
+        const bool v = i < F;
+        wave_sync();
+        const u32x4 r = m.rec_g[v ? i : 0u];
+        if (v && i < m.rec_n) m.rec_l[i] = r;
+        const uint32_t c = cls(r[1]);
+        uint64_t h = ballot(v && r[3] == kNone);
+        for (; h != 0ull; h &= h - 1ull) {
+          const uint32_t l = ctz64(h), cl = rdlane(c, l);
+          set_head(cl, base + l);
+          bit_set(cl);
+        }
+      }
+    }
+    for (uint32_t base = 0; base < L && base < m.ll_n; base += 64u) {
+      const uint32_t i = base + lane;
+      wave_sync();
+      if (i < L && i < m.ll_n) m.ll[i] = m.gl[i];
+    }
+    wave_order();
+  }
+  // Entry (key, value) of rank r among F in n chunks, into chunk slot memory.
+  __device__ __forceinline__ void place(HDA_GLOBAL uint8_t* g, uint32_t r, uint32_t n,
+                                        uint32_t key, uint32_t val) const {
+    const uint32_t c = ((r + 1u) * n - 1u) / F, p = r - c * F / n;
+    u32x2 v;
+    v[0] = key; v[1] = val;
+    *(HDA_GLOBAL u32x2*)(g + (uint64_t)c * TA::CB + p * 8u) = v;
+  }
+  // Chunks 0 .. n - 1 from the slots place() filled, and their directory.
+  template <typename T>
+  __device__ __forceinline__ void build(T& t, uint32_t n) {
+    for (uint32_t c = 0; c < n; ++c) {
+      const uint32_t cnt = (c + 1u) * F / n - c * F / n;
+      const bool in = lane_id() < cnt;
+      wave_sync();
+      const u32x2 v = *(const HDA_GLOBAL u32x2*)(t.gb + (uint64_t)c * T::CB + lane_id() * 8u);
+      const typename T::Row r{in ? v[0] : kNone, in ? v[1] : T::kSentS};
+      t.store(c, r);
+      dir_put(t.dsl, c, c);
+      t.describe(c, r, cnt);
+    }
+    t.nc = n;
+#pragma unroll
+    for (int k = 0; k < T::ND; ++k) t.used[k] = lanes_below(n > 64u * k ? n - 64u * k : 0u);
   }
 
   // Continue a heap that ran with fewer directory registers: the same

@@ -143,6 +143,19 @@ __device__ __forceinline__ Cold general_tiers(const ReplayParams& p, HDA_LDS uin
   return c;
 }
 
+// The general core's tiers inside a wave's ordered-core slot, for the heap
+// that goes there instead (32 cap_free + 8 cap_live bytes hold its 12 + 8).
+__device__ __forceinline__ Cold slot_tiers(const ReplayParams& p, HDA_GLOBAL uint8_t* slot) {
+  Cold c;
+  c.lf = nullptr; c.lst = nullptr; c.ll = nullptr;
+  c.gf = (HDA_GLOBAL Ent*)slot;
+  c.gst = (HDA_GLOBAL uint32_t*)(slot + (size_t)p.cap_free * 8);
+  c.gl = (HDA_GLOBAL Ent*)(slot + (size_t)p.cap_free * 12);
+  c.kf = 0; c.kl = 0;
+  c.cf = p.cap_free; c.cl = p.cap_live;
+  return c;
+}
+
 // General path for every heap (tables in LDS, then device memory).
 __global__ void __launch_bounds__(1024) general_kernel(ReplayParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -155,27 +168,94 @@ __global__ void __launch_bounds__(1024) general_kernel(ReplayParams p) {
   });
 }
 
+// The three parts of the lean path (hda_replay_body.h) as functions of their
+// own: each is compiled by itself, so that the lean request loops do not
+// share a register budget with the ordered and general cores (all in one
+// function they took the kernel past 128 VGPRs and into scratch in the loops;
+// calls from within the lean part cost the loops 2-3 %).  The calls are three
+// per heap at most.  Arguments are wave-uniform but for LeanExit::cnt; the
+// kernel's parameters are read from where the launch put them.
+typedef const __attribute__((address_space(4))) ReplayParams* LaunchParams;
+
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
+}
+
+// What a part works with: the launch's parameters, the wave's pool and its
+// device-memory slot for a heap that outgrows the pool -- the ordered core's
+// (which also holds the general core's tiers), or the general core's alone.
+struct WaveEnv {
+  ReplayParams p;
+  LeanLds lds;
+  HDA_GLOBAL uint8_t* ord;
+  Cold c;
+  __device__ __forceinline__ WaveEnv(LaunchParams lp, uint32_t pool, uint32_t slot) {
+    __builtin_memcpy(&p, (const void*)(LaunchParams)uniform64((uint64_t)lp), sizeof(p));
+    lds.base = (HDA_LDS uint8_t*)(uintptr_t)uniform(pool);
+    lds.bytes = p.lds_wave_bytes;
+    slot = uniform(slot);
+    ord = nullptr;
+    if (p.ord_spill) {
+      ord = (HDA_GLOBAL uint8_t*)(p.ord_spill + slot * p.ord_spill_stride);
+      c = slot_tiers(p, ord);
+    } else {
+      c = general_tiers(p, lds.base, slot);
+    }
+  }
+};
+__device__ __forceinline__ LeanExit uniform_exit(LeanExit x) {
+  x.st = (int32_t)uniform((uint32_t)x.st);
+  x.pos = (int64_t)uniform64((uint64_t)x.pos);
+  x.F = uniform(x.F); x.L = uniform(x.L);
+  x.rover = uniform(x.rover); x.clock = uniform(x.clock);
+  return x;
+}
+
+template <int ALGO, int RF>
+__device__ __attribute__((noinline)) LeanExit lean_call(LaunchParams lp, uint32_t pool,
+                                                        uint32_t slot, int32_t heap) {
+  const WaveEnv e(lp, pool, slot);
+  return lean_start<ALGO, RF>(e.p, e.lds, e.c, (int64_t)(int32_t)uniform((uint32_t)heap), e.ord);
+}
+template <int ALGO>
+__device__ __attribute__((noinline)) void ord_call(LaunchParams lp, uint32_t pool, uint32_t slot,
+                                                   int32_t heap, LeanExit x) {
+  const WaveEnv e(lp, pool, slot);
+  ord_continue<ALGO>(e.p, e.lds, e.ord, (int64_t)(int32_t)uniform((uint32_t)heap),
+                     uniform_exit(x));
+}
+template <int ALGO>
+__device__ __attribute__((noinline)) void general_call(LaunchParams lp, uint32_t pool,
+                                                       uint32_t slot, int32_t heap, LeanExit x) {
+  const WaveEnv e(lp, pool, slot);
+  general_continue<ALGO>(e.p, e.c, (int64_t)(int32_t)uniform((uint32_t)heap), uniform_exit(x));
+}
+template <int ALGO, int RF>
+__device__ __forceinline__ void lean_heap(LaunchParams lp, uint32_t pool, uint32_t slot,
+                                          int32_t heap) {
+  const LeanExit x = lean_call<ALGO, RF>(lp, pool, slot, heap);
+  const int32_t next = (int32_t)uniform((uint32_t)x.next);
+  if (next == LeanExit::kOrdered) ord_call<ALGO>(lp, pool, slot, heap, x);
+  if (next == LeanExit::kGeneral) general_call<ALGO>(lp, pool, slot, heap, x);
+}
+
 // Lean path with RF free-table chunks in VGPRs; each heap runs the code of
 // its own algorithm.
 template <int RF>
 __global__ void __launch_bounds__(1024) lean_kernel(ReplayParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const uint32_t wave = uniform(threadIdx.x >> 6);  // the same in every lane of the wave
-  HDA_LDS uint8_t* mine = (HDA_LDS uint8_t*)smem + (size_t)wave * p.lds_wave_bytes;
-  const uint64_t slot = (uint64_t)blockIdx.x * p.waves_per_group + wave;
-  LeanLds lds;
-  lds.base = mine;
-  lds.bytes = p.lds_wave_bytes;
-  // the general core's tiers for a heap that outgrows the pool: this wave's
-  // device-memory slot (no LDS part)
-  const Cold c = general_tiers(p, mine, slot);
+  const uint32_t pool = (uint32_t)(uintptr_t)((HDA_LDS uint8_t*)smem) + wave * p.lds_wave_bytes;
+  const uint32_t slot = blockIdx.x * p.waves_per_group + wave;
+  const LaunchParams lp = (LaunchParams)__builtin_amdgcn_kernarg_segment_ptr();
   for_each_heap(p, slot, [&](int64_t heap) __attribute__((always_inline)) {
+    const int32_t h = (int32_t)heap;  // (n_heaps is below 2^31)
     switch (p.algo[heap]) {
-      case kFirstFit: lean_one_heap<kFirstFit, RF>(p, lds, c, heap); break;
-      case kNextFit: lean_one_heap<kNextFit, RF>(p, lds, c, heap); break;
-      case kBestFit: lean_one_heap<kBestFit, RF>(p, lds, c, heap); break;
-      case kSegFit: lean_one_heap<kSegFit, RF>(p, lds, c, heap); break;
-      case kTlsf: lean_one_heap<kTlsf, RF>(p, lds, c, heap); break;
+      case kFirstFit: lean_heap<kFirstFit, RF>(lp, pool, slot, h); break;
+      case kNextFit: lean_heap<kNextFit, RF>(lp, pool, slot, h); break;
+      case kBestFit: lean_heap<kBestFit, RF>(lp, pool, slot, h); break;
+      case kSegFit: lean_heap<kSegFit, RF>(lp, pool, slot, h); break;
+      case kTlsf: lean_heap<kTlsf, RF>(lp, pool, slot, h); break;
       default: reject_heap(p, heap); break;  // the bitmask allocator has its own kernel
     }
   });
@@ -245,12 +325,13 @@ struct Pass {
   uint32_t W = 1, kf = 0, kl = 0, sf = 0, sl = 0, lds_wave = 0, lds_group = 0;
   uint32_t lds_free = 0, lds_live = 0;  // the LDS residency as the tuning states it
   int64_t groups = 1, slots = 1;
-  size_t off_free = 0, off_stamp = 0, off_live = 0;
+  size_t off_free = 0, off_stamp = 0, off_live = 0, off_ord = 0, ord_stride = 0;
 };
 
 struct Plan {
   const KernelSet* set;
   bool lean;
+  bool ord_spill = false;  // heaps that outgrow the lean pool go to the ordered core
   uint32_t capF, capL;
   Pass main;
   // the ordered-core launch: the first `heavy` heaps of the order, one wave
@@ -276,7 +357,10 @@ int occupancy_groups(const void* fn, uint32_t W, uint32_t lds_group, int cus, in
 }
 
 // Fill defaults and derive the launches and the workspace layout.
-bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl) {
+// `may_ord`: heaps that outgrow the lean pool may go to the ordered core,
+// whose slots take 32 rather than 12 bytes per free entry of capacity; false
+// plans the smaller workspace.
+bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl, bool may_ord = true) {
   if (!d || d->n_heaps < 0 || d->meta_free < 0 || d->meta_live < 0) return false;
   if (d->n_heaps > INT32_MAX) return false;
   const hda_tuning& tu = d->tuning;
@@ -326,6 +410,8 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl) {
   }
   m.lds_group = m.lds_wave * W;
   if (m.lds_group > dc->max_lds) return false;
+  pl->ord_spill = lean && may_ord && capF <= kOrdMaxFree && m.lds_wave >= kOrdMinPool;
+  if (pl->ord_spill) m.sf = m.sl = 0;
   // the ordered-core launch (persistent replays only)
   const int64_t heavy = persistent ? std::min<int64_t>(tu.heavy_heaps, d->n_heaps) : 0;
   int heavy_cus = 0;
@@ -365,8 +451,25 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl) {
   m.off_free = off; off = align_up(off + (size_t)m.slots * m.sf * 8);
   m.off_stamp = off; off = align_up(off + (size_t)m.slots * m.sf * 4);
   m.off_live = off; off = align_up(off + (size_t)m.slots * m.sl * 8);
+  m.off_ord = off;
+  m.ord_stride = pl->ord_spill ? align_up(ord_spill_bytes(capF, capL)) : 0;
+  off += (size_t)m.slots * m.ord_stride;
   pl->off_ord = off; off = align_up(off + (size_t)pl->heavy_groups * pl->heavy_stride);
   pl->bytes = off;
+  return true;
+}
+
+// The plan for a workspace of `have` bytes: with ordered-core slots if they
+// fit, else the smaller one.  False if the descriptor is invalid; *fits says
+// whether the workspace holds the plan.
+bool plan_for(const hda_batch_desc* d, bool persistent, size_t have, Plan* pl, bool* fits) {
+  *pl = Plan();
+  if (!make_plan(d, persistent, pl)) return false;
+  if (pl->bytes > have && pl->ord_spill) {
+    *pl = Plan();
+    if (!make_plan(d, persistent, pl, false)) return false;
+  }
+  *fits = pl->bytes <= have;
   return true;
 }
 
@@ -418,6 +521,8 @@ ReplayParams replay_params(const hda_batch_desc* d, const Plan& pl) {
   p.use_queue = 1;
   p.list_lo = pl.heavy;
   p.list_hi = INT64_MAX;
+  p.ord_spill = pl.ord_spill ? ws + ps.off_ord : nullptr;
+  p.ord_spill_stride = ps.ord_stride;
   return p;
 }
 
@@ -531,9 +636,10 @@ int hda_replay_resolve(const hda_batch_desc* d, hda_tuning* out) {
 
 int hda_replay(const hda_batch_desc* d, void* stream) {
   Plan pl;
-  if (!desc_ok(d) || !make_plan(d, true, &pl)) return HDA_E_INVAL;
+  bool fits = false;
+  if (!desc_ok(d) || !plan_for(d, true, d->workspace_bytes, &pl, &fits)) return HDA_E_INVAL;
   if (d->n_heaps == 0) return HDA_OK;
-  if (!d->workspace || d->workspace_bytes < pl.bytes) return HDA_E_RANGE;
+  if (!d->workspace || !fits) return HDA_E_RANGE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (!set_lds_attrs(pl)) return HDA_E_DEVICE;
   return enqueue(d, pl, s);
@@ -541,9 +647,10 @@ int hda_replay(const hda_batch_desc* d, void* stream) {
 
 int hda_replay_per_heap(const hda_batch_desc* d, void* stream) {
   Plan pl;
-  if (!desc_ok(d) || !make_plan(d, false, &pl)) return HDA_E_INVAL;
+  bool fits = false;
+  if (!desc_ok(d) || !plan_for(d, false, d->workspace_bytes, &pl, &fits)) return HDA_E_INVAL;
   if (d->n_heaps == 0) return HDA_OK;
-  if (!d->workspace || d->workspace_bytes < pl.bytes) return HDA_E_RANGE;
+  if (!d->workspace || !fits) return HDA_E_RANGE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (!set_lds_attrs(pl)) return HDA_E_DEVICE;
   int rc = classify(d, pl, s);
@@ -852,10 +959,11 @@ extern "C" {
 
 int hda_replay_static(const hda_batch_desc* d, void* stream) {
   Plan pl;
-  if (!desc_ok(d) || !make_plan(d, true, &pl)) return HDA_E_INVAL;
+  bool fits = false;
+  if (!desc_ok(d) || !plan_for(d, true, kStaticScratchBytes, &pl, &fits)) return HDA_E_INVAL;
   if (pl.heavy > 0) return HDA_E_INVAL;  // events and a second stream: use hda_replay
   if (d->n_heaps == 0) return HDA_OK;
-  if (pl.bytes > kStaticScratchBytes) return HDA_E_RANGE;
+  if (!fits) return HDA_E_RANGE;
   uint8_t* ws = static_scratch();
   if (!ws) return HDA_E_DEVICE;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -880,8 +988,11 @@ extern "C" {
 
 int hda_replay_capture(const hda_batch_desc* d, hda_graph** out) {
   Plan pl;
-  if (!out || !desc_ok(d) || !make_plan(d, true, &pl) || d->n_heaps == 0) return HDA_E_INVAL;
-  if (!d->workspace || d->workspace_bytes < pl.bytes) return HDA_E_RANGE;
+  bool fits = false;
+  if (!out || !desc_ok(d) || !plan_for(d, true, d->workspace_bytes, &pl, &fits) ||
+      d->n_heaps == 0)
+    return HDA_E_INVAL;
+  if (!d->workspace || !fits) return HDA_E_RANGE;
   if (!set_lds_attrs(pl)) return HDA_E_DEVICE;
   if (pl.heavy > 0 && !fork_stream()) return HDA_E_DEVICE;
   hipStream_t cs = nullptr;

@@ -48,6 +48,10 @@ struct ReplayParams {
   uint32_t ord_slot_bytes;
   uint8_t* ord_dev;
   uint64_t ord_dev_stride;
+  // lean core: each wave's device slot for heaps that outgrow the pool
+  // (ord_spill_bytes), or null
+  uint8_t* ord_spill;
+  uint64_t ord_spill_stride;
 };
 
 // Validate heap parameters; on success fill the uniform heap registers.
@@ -216,27 +220,22 @@ __device__ __forceinline__ void replay_heap(const ReplayParams& p, const Cold& c
   finish_heap(p, w, heap, st);
 }
 
-// Lean path (hda_lean.h).  A heap whose tables outgrow the lean tiers moves
-// them into the general core's layout -- the same LDS bytes, then the wave's
-// device-memory spill slot -- and continues there from the request that
-// did not fit.
-template <int ALGO, int RF>
-__device__ void lean_replay_heap(const ReplayParams& p, const LeanLds& lds, const Cold& c,
-                                 const HeapRegs& regs, int64_t heap) {
-  LeanHeap<ALGO, RF> w(lds, regs, p.cap_free, p.cap_live);
-  w.init();
-  int32_t st = 0;
-  const int64_t b1 = p.req_off[heap + 1];
-  const int64_t pos = run_requests<ALGO>(p, w, p.req_off[heap], b1, w.shift, w.arena, st);
-  if (pos == b1) {
+// Requests [pos, to) of a heap on the ordered core, from an OrdHeap with one
+// directory register (kept while the tables fit 64 chunks) or with all of
+// them.
+template <int ALGO>
+__device__ __forceinline__ void ord_run(const ReplayParams& p, const OrdMem& m,
+                                        OrdHeap<ALGO, 1>& w, const HeapRegs& regs, int64_t pos,
+                                        int64_t to, int64_t heap, int32_t st) {
+  pos = run_requests<ALGO>(p, w, pos, to, regs.shift, regs.arena, st);
+  if (pos == to) {
     finish_heap(p, w, heap, st);
     return;
   }
-  WaveHeap<ALGO, 0, 0> g(c, regs, p.cap_free, p.cap_live);
-  w.migrate(c, g.h);
-  if (lane_id() == 0 && p.migrated) atomicAdd(p.migrated, 1u);
-  run_requests<ALGO>(p, g, pos, b1, g.h.shift, g.h.arena, st);
-  finish_heap(p, g, heap, st);
+  OrdHeap<ALGO, kOrdDir> w2(m, regs, p.cap_free, p.cap_live);
+  w2.take(w);
+  run_requests<ALGO>(p, w2, pos, to, regs.shift, regs.arena, st);
+  finish_heap(p, w2, heap, st);
 }
 
 // Heap with invalid parameters: every result and the status are E_INVAL.
@@ -263,16 +262,102 @@ __device__ __forceinline__ void replay_one_heap(const ReplayParams& p, const Col
   replay_heap<ALGO, RF, RL>(p, c, h, heap);
 }
 
-// Lean replay of one heap known to use algorithm ALGO.
+// Lean path (hda_lean.h).  A heap whose tables outgrow the lean pool goes on
+// from the request that did not fit: on the ordered core (hda_ordered.h) in
+// the same LDS and the wave's device slot `ord`, where every request costs
+// the same however large the tables are; or, without such a slot or with
+// more free blocks than adopt() takes, on the general core in the wave's
+// spill slot, which scans the whole table for every request.  1,000 ragged
+// next-fit heaps whose tables reach thousands of entries: 17.0 ms on the
+// general core, 6.5 ms on the ordered core (15,000 requests each); the
+// uneven batch at the default tuning: 512 against 172 ms.
+//
+// Where a heap stands when it leaves the lean core.
+struct LeanExit {
+  enum : int32_t { kDone = 0, kOrdered = 1, kGeneral = 2 };
+  int32_t next, st;
+  int64_t pos;               // the first request not run
+  uint32_t F, L, rover, clock;
+  uint32_t cnt;              // per lane (HeapRegs::cnt)
+};
+
+template <int ALGO>
+__device__ __forceinline__ OrdMem ord_spill_mem(const ReplayParams& p, HDA_LDS uint8_t* pool,
+                                                uint32_t pool_bytes, HDA_GLOBAL uint8_t* ord) {
+  return ord_mem(ALGO, pool, pool_bytes, pool_bytes / 2u, ord, p.cap_live,
+                 (uint32_t)ord_area_bytes(p.cap_free));
+}
+
+// A heap on the lean core from its first request: to its end, or until its
+// tables lie in the ordered core's slot (OrdHeap::stage) or in tiers c.
 template <int ALGO, int RF>
-__device__ __forceinline__ void lean_one_heap(const ReplayParams& p, const LeanLds& lds,
-                                              const Cold& c, int64_t heap) {
+__device__ __forceinline__ LeanExit lean_start(const ReplayParams& p, const LeanLds& lds,
+                                               const Cold& c, int64_t heap,
+                                               HDA_GLOBAL uint8_t* ord) {
+  LeanExit x{LeanExit::kDone, 0, 0, 0u, 0u, 0u, 0u, 0u};
   HeapRegs h;
   if (!heap_params(p, heap, h) || h.algo != ALGO) {
     reject_heap(p, heap);
-    return;
+    return x;
   }
-  lean_replay_heap<ALGO, RF>(p, lds, c, h, heap);
+  LeanHeap<ALGO, RF> w(lds, h, p.cap_free, p.cap_live);
+  w.init();
+  const int64_t b1 = p.req_off[heap + 1];
+  x.pos = run_requests<ALGO>(p, w, p.req_off[heap], b1, w.shift, w.arena, x.st);
+  if (x.pos == b1) {
+    finish_heap(p, w, heap, x.st);
+    return x;
+  }
+  if (lane_id() == 0 && p.migrated) atomicAdd(p.migrated, 1u);
+  // (one directory register describes 64 chunks; adopt() fills 56 entries of
+  // each, so that many free blocks leave a chunk to spare)
+  if (ord != nullptr && w.F <= ord_adopt_max(p.cap_free) && w.F <= 56u * 63u) {
+    x.next = LeanExit::kOrdered;
+    OrdHeap<ALGO, 1>(ord_spill_mem<ALGO>(p, lds.base, lds.bytes, ord), h, p.cap_free,
+                     p.cap_live).stage(w);
+  } else {
+    x.next = LeanExit::kGeneral;
+    w.migrate(c, h);
+    x.cnt = h.cnt;
+  }
+  x.F = w.F; x.L = w.L; x.rover = w.rover; x.clock = w.clock;
+  return x;
+}
+
+// The rest of a heap that left the lean core for the ordered core, in the
+// pool its lean tables had, or for the general core.
+template <int ALGO>
+__device__ __forceinline__ void ord_continue(const ReplayParams& p, const LeanLds& lds,
+                                             HDA_GLOBAL uint8_t* ord, int64_t heap,
+                                             const LeanExit& x) {
+  HeapRegs h;
+  if (!heap_params(p, heap, h)) return;  // (they were valid when the heap started)
+  const OrdMem m = ord_spill_mem<ALGO>(p, lds.base, lds.bytes, ord);
+  OrdHeap<ALGO, 1> o(m, h, p.cap_free, p.cap_live);
+  o.adopt(x.F, x.L, x.rover, SegKey<ALGO>::kShift);
+  ord_run<ALGO>(p, m, o, h, x.pos, p.req_off[heap + 1], heap, x.st);
+}
+template <int ALGO>
+__device__ __forceinline__ void general_continue(const ReplayParams& p, const Cold& c,
+                                                 int64_t heap, const LeanExit& x) {
+  HeapRegs h;
+  if (!heap_params(p, heap, h)) return;
+  h.F = x.F; h.L = x.L; h.rover = x.rover; h.clock = x.clock; h.cnt = x.cnt;
+  WaveHeap<ALGO, 0, 0> g(c, h, p.cap_free, p.cap_live);
+  int32_t st = x.st;
+  run_requests<ALGO>(p, g, x.pos, p.req_off[heap + 1], h.shift, h.arena, st);
+  finish_heap(p, g, heap, st);
+}
+
+// Lean replay of one heap known to use algorithm ALGO, all of it in place
+// (the GPU kernels call the three parts out of line, hda_replay.hip).
+template <int ALGO, int RF>
+__device__ __forceinline__ void lean_one_heap(const ReplayParams& p, const LeanLds& lds,
+                                              const Cold& c, int64_t heap,
+                                              HDA_GLOBAL uint8_t* ord = nullptr) {
+  const LeanExit x = lean_start<ALGO, RF>(p, lds, c, heap, ord);
+  if (x.next == LeanExit::kOrdered) ord_continue<ALGO>(p, lds, ord, heap, x);
+  if (x.next == LeanExit::kGeneral) general_continue<ALGO>(p, c, heap, x);
 }
 
 // Any algorithm (used where one program must serve every heap).
@@ -299,20 +384,9 @@ template <int ALGO>
 __device__ __forceinline__ void ord_replay_heap(const ReplayParams& p, HDA_LDS uint8_t* pool,
                                 HDA_GLOBAL uint8_t* dev, const HeapRegs& regs, int64_t heap) {
   const OrdMem m = ord_mem(ALGO, pool, p.ord_pool_bytes, p.ord_slot_bytes, dev, p.cap_live);
-  // one directory register while the tables fit 64 chunks, then two
   OrdHeap<ALGO, 1> w(m, regs, p.cap_free, p.cap_live);
   w.init();
-  int32_t st = 0;
-  const int64_t b1 = p.req_off[heap + 1];
-  const int64_t pos = run_requests<ALGO>(p, w, p.req_off[heap], b1, regs.shift, regs.arena, st);
-  if (pos == b1) {
-    finish_heap(p, w, heap, st);
-    return;
-  }
-  OrdHeap<ALGO, kOrdDir> w2(m, regs, p.cap_free, p.cap_live);
-  w2.take(w);
-  run_requests<ALGO>(p, w2, pos, b1, regs.shift, regs.arena, st);
-  finish_heap(p, w2, heap, st);
+  ord_run<ALGO>(p, m, w, regs, p.req_off[heap], p.req_off[heap + 1], heap, 0);
 }
 
 __device__ __forceinline__ void ord_any_heap(const ReplayParams& p, HDA_LDS uint8_t* pool,

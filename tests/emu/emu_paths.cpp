@@ -13,13 +13,29 @@ struct PathJob {
   Ent* live;
   uint32_t kn;             // summaries kept in "LDS"
   uint64_t max_granules;
+  Cold c;                  // the other allocators: the general core's tiers
+  uint8_t* ord;            // and the ordered core's device slot, or null
   int done;
 };
 PathJob g_path;
 
+template <int RF>
+void spill_any(PathJob& j) {
+  switch (j.p.algo[j.heap]) {
+    case kFirstFit: lean_one_heap<kFirstFit, RF>(j.p, j.lds, j.c, j.heap, j.ord); break;
+    case kNextFit: lean_one_heap<kNextFit, RF>(j.p, j.lds, j.c, j.heap, j.ord); break;
+    case kBestFit: lean_one_heap<kBestFit, RF>(j.p, j.lds, j.c, j.heap, j.ord); break;
+    case kSegFit: lean_one_heap<kSegFit, RF>(j.p, j.lds, j.c, j.heap, j.ord); break;
+    default: lean_one_heap<kTlsf, RF>(j.p, j.lds, j.c, j.heap, j.ord); break;
+  }
+}
+
 void path_main() {
-  bitmap_lean_heap(g_path.p, g_path.lds, g_path.bits, g_path.nodes, g_path.live, g_path.kn,
-                   g_path.max_granules, g_path.heap);
+  if (g_path.bits)
+    bitmap_lean_heap(g_path.p, g_path.lds, g_path.bits, g_path.nodes, g_path.live, g_path.kn,
+                     g_path.max_granules, g_path.heap);
+  else
+    spill_any<2>(g_path);
   // a finished lane keeps handing over until every lane has finished
   g_path.done++;
   for (;;) {
@@ -92,4 +108,43 @@ extern "C" int emu_path_replay(int64_t H, const int64_t* arena, const int64_t* a
   }
   emu_wave = nullptr;
   return rc;
+}
+
+// Replay H heaps on the lean core in a pool of `pool` bytes with an
+// ordered-core slot for those that outgrow it (moved[h] = 1).
+extern "C" int emu_spill_replay(int64_t H, const int64_t* arena, const int64_t* align,
+                                const int32_t* algo, const int64_t* req_off, const int64_t* req,
+                                int64_t* res, int64_t* state, const int64_t* state_off,
+                                int64_t* state_len, int32_t* status, uint32_t pool,
+                                uint32_t cap_free, uint32_t cap_live, uint8_t* moved) {
+  std::memset(&g_path.p, 0, sizeof(g_path.p));
+  ReplayParams& p = g_path.p;
+  p.arena = arena; p.align = align; p.algo = algo; p.req_off = req_off; p.req = req;
+  p.res = res; p.state = state; p.state_off = state_off; p.state_len = state_len;
+  p.status = status; p.cap_free = cap_free; p.cap_live = cap_live;
+  uint32_t migrated = 0;
+  p.migrated = &migrated;
+  std::vector<std::vector<uint8_t>> stacks(64, std::vector<uint8_t>(256 * 1024));
+  EmuWave w;
+  emu_wave = &w;
+  for (int64_t h = 0; h < H; ++h) {
+    std::vector<uint64_t> mem(pool / 8u + 2u, 0xA5A5A5A5A5A5A5A5ull);
+    std::vector<uint64_t> slot(ord_spill_bytes(cap_free, cap_live) / 8u, mem[0]);
+    g_path.lds.base = reinterpret_cast<uint8_t*>(mem.data());
+    g_path.lds.bytes = pool;
+    g_path.heap = h;
+    g_path.bits = nullptr;
+    g_path.ord = reinterpret_cast<uint8_t*>(slot.data());
+    Cold& c = g_path.c;
+    c.lf = nullptr; c.lst = nullptr; c.ll = nullptr;
+    c.gf = reinterpret_cast<Ent*>(g_path.ord);
+    c.gst = reinterpret_cast<uint32_t*>(g_path.ord + size_t(cap_free) * 8);
+    c.gl = reinterpret_cast<Ent*>(g_path.ord + size_t(cap_free) * 12);
+    c.kf = 0; c.kl = 0; c.cf = cap_free; c.cl = cap_live;
+    const uint32_t before = migrated;
+    run_path(w, stacks);
+    moved[h] = migrated != before;
+  }
+  emu_wave = nullptr;
+  return 0;
 }

@@ -1,6 +1,7 @@
 """Replay paths that change core mid-trace, as lockstep-emulated waves on the
 CPU, against the oracle: the bitmask allocator replayed from the lean core's
-table of free blocks, continuing on the flags once its pool is too small."""
+table of free blocks, continuing on the flags once its pool is too small, and
+lean-core heaps continuing on the ordered core."""
 import ctypes
 import os
 import subprocess
@@ -96,3 +97,50 @@ def test_bitmap_table_edges(lib):
         res, states, status, _ = bitmap_replay(lib, b, pool, cap_live=16)
         assert status[0] == -4 == want[2][0]
         assert np.array_equal(res, want[0]) and np.array_equal(states[0], want[1][0])
+
+
+def spill_replay(lib, b, pool, cap_free=4096, cap_live=8192):
+    res, state, so, sl, status, moved = buffers(b, lambda n: n + 1)
+    P = lambda a: ctypes.c_void_p(a.ctypes.data)  # noqa: E731
+    arena, align = np.ascontiguousarray(b.arena), np.ascontiguousarray(b.align)
+    algo, off = np.ascontiguousarray(b.algo, np.int32), np.ascontiguousarray(b.req_off)
+    req = np.ascontiguousarray(b.req)
+    lib.emu_spill_replay(ctypes.c_int64(b.heaps), P(arena), P(align), P(algo), P(off), P(req),
+                         P(res), P(state), P(so), P(sl), P(status), ctypes.c_uint32(pool),
+                         ctypes.c_uint32(cap_free), ctypes.c_uint32(cap_live), P(moved))
+    return res, [state[so[h]:so[h] + sl[h]] for h in range(b.heaps)], status, moved
+
+
+# TLSF's list heads take 8 KiB of the pool
+def spill_pool(algo, bytes_):
+    return bytes_ + (8192 if algo == W.TLSF else 0)
+
+
+@pytest.mark.parametrize("algo", (0, 1, 2, 3, 4))
+@pytest.mark.parametrize("pool", (512, 2048))
+def test_lean_heap_continues_on_the_ordered_core(lib, algo, pool):
+    """The tables outgrow the pool mid-trace, with one chunk of free blocks or
+    several: small blocks, partial frees, and the state the class lists were
+    left in."""
+    n = 5000 if algo == W.TLSF else 2500
+    b = W.concat([W.uniform_batch(seed=7, heaps=1, arena=1 << 22, align=16, n=n, p_alloc=0.75,
+                                  lo=16, hi=4000, algo=algo, p_partial=0.3),
+                  W.uniform_batch(seed=8, heaps=1, n=1200, algo=algo, p_alloc=0.7)])
+    res, states, status, moved = spill_replay(lib, b, spill_pool(algo, pool))
+    check(b, res, states, status)
+    assert moved[0] == 1
+
+
+@pytest.mark.parametrize("algo", (0, 1, 2, 3, 4))
+def test_ordered_continuation_at_capacity(lib, algo):
+    """Capacities reached after the move: the same requests are refused and
+    the same state is left as on the general core.  With a capacity of 64
+    free blocks, a heap that brings more than 48 goes to the general core."""
+    b = W.uniform_batch(seed=9, heaps=2, n=1800, algo=algo, p_alloc=0.65)
+    for cap in (64, 128):
+        want = emu.replay(b, kf=64, kl=64, cf=cap, cl=192, shape=0)
+        res, states, status, moved = spill_replay(lib, b, 512, cap_free=cap, cap_live=192) \
+            if algo != W.TLSF else spill_replay(lib, b, 8192 + 512, cap_free=cap, cap_live=192)
+        assert np.array_equal(res, want[0]) and np.array_equal(status, want[2])
+        for h in range(b.heaps):
+            assert np.array_equal(states[h], want[1][h])
