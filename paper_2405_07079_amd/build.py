@@ -19,6 +19,10 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
          # regions as if they could diverge made the request loops copy
          # the heap's registers on every request
          "-mllvm", "-structurizecfg-skip-uniform-regions=true",
+         # blocks reached only by a taken branch start on a fetch boundary (no
+         # instruction is added to a path): 1-3 % on the replay kernels, and
+         # figures that do not move with the layout of other code
+         "-mllvm", "-align-all-nofallthru-blocks=5",
          "-Wall", "-Wno-unused-function"]
 
 

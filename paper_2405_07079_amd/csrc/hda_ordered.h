@@ -15,23 +15,27 @@
 // from it.  So while there are two or more chunks each holds at least 32
 // entries, and the directory's 64 D chunks always hold 2,048 D free blocks.
 //
-// A free block's entry is keyed by its END granule address.  Free blocks do
-// not overlap, so this is also address order, and Alg. 1 / Alg. 4 cut an
+// A free block's entry is keyed by its LAST granule.  Free blocks do not
+// overlap, so this is also address order, and Alg. 1 / Alg. 4 cut an
 // allocation from the low end of a block: the remainder keeps its end, so
 // splitting a block rewrites its size (or its record) and never its place.
-// The block ending at a freed block's start is an exact key match; the one
-// after it is the next entry.
+// The block ending right below a freed block's start is an exact key match;
+// the one after it is the next entry.  No block's last granule is kNone
+// (arenas end at 2^32 - 1 granules), so kNone fills the unused entries and
+// directory lanes and every search is one strict comparison with no mask:
+// "last granule < x" is "end <= x".
 //
 // Per algorithm:
-//  * first fit (Sec. II-A): entries (end, size); the first chunk whose
+//  * first fit (Sec. II-A): entries (last granule, size); the first chunk whose
 //    largest block fits, then the first fitting entry in it.
 //  * next fit (Sec. II-A, Sec. IV): the first block ending past the rover
 //    is located like a key; the search runs on from there through the
 //    directory and wraps once.
-//  * best fit (Alg. 3): entries (end, size) and a second sorted chunk table
-//    of keys (size, end) -- among blocks of one size the lowest end is the
-//    lowest address; the smallest key at or above (s, 0) is the best fit.
-//  * segregated fit (Alg. 4-5) and TLSF (Sec. V-B): entries (end, record).
+//  * best fit (Alg. 3): entries (last granule, size) and a second sorted
+//    chunk table of keys (size, last granule) -- among blocks of one size the
+//    lowest is the lowest address; the smallest key at or above (s, 0) is the best fit.
+//  * segregated fit (Alg. 4-5) and TLSF (Sec. V-B): entries (last granule,
+//    record).
 //    A record holds the block's address and size and its class-list links
 //    (next and previous record, NIL = kNone), as Alg. 4-5 keep them; record
 //    numbers never change while a block is free, so unlinking and pushing
@@ -42,6 +46,17 @@
 //    and a VGPR (TLSF's second level: lane fl holds level fl's 32 bits).
 //    The paper's address-keyed hash lookup ht[addr] becomes the key lookup
 //    in the table.
+//
+// What bounds it: one wave alone issues an instruction every four clocks and
+// waits about 130 for each dependent LDS read, and no other wave hides that.
+// So searches take no masks, a chunk's largest block is reduced anew only
+// when that block goes, the record given back last is taken next, the next
+// free's victim is loaded while the current request runs, and the LDS side of
+// every access falls through.  First 100,000-300,000 requests of the 256 GiB
+// traces, per request: first fit 466 -> 396 ns, next fit 521 -> 435, best fit
+// 722 -> 652, segregated fit 657 -> 617, TLSF 815 -> 733.  (Tried and not
+// kept: best fit's remainder chunk loaded before the old key is removed, 2 %
+// slower; writing a chunk's first key only when it changes, 2-4 % slower.)
 //
 // Results equal those of the other cores and the oracle: selection,
 // splitting, merging and the class lists follow the same definitions.
@@ -64,6 +79,12 @@ namespace hda {
 // pointers of any address space).
 typedef uint32_t u32x2 __attribute__((vector_size(8)));
 typedef uint32_t u32x4 __attribute__((vector_size(16)));
+
+// A branch whose other side is out of the way: a lone wave pays a taken
+// branch with an instruction fetch, so the LDS side of a table access and
+// the common outcomes fall through.
+__device__ __forceinline__ bool likely(bool c) { return __builtin_expect(c, true); }
+__device__ __forceinline__ bool unlikely(bool c) { return __builtin_expect(c, false); }
 
 // Wave-wide maximum of a u32 (every lane active).
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) { return ~wave_min(~v); }
@@ -95,9 +116,13 @@ __device__ __forceinline__ uint32_t dir_get(const uint32_t (&v)[D], uint32_t i) 
 }
 template <int D>
 __device__ __forceinline__ void dir_put(uint32_t (&v)[D], uint32_t i, uint32_t x) {
-  const bool me = lane_id() == (i & 63u);
+  if constexpr (D == 1) {
+    v[0] = put_lane(v[0], i, x);
+  } else {
+    const bool me = lane_id() == (i & 63u);
 #pragma unroll
-  for (int k = 0; k < D; ++k) v[k] = (me && (i >> 6) == (uint32_t)k) ? x : v[k];
+    for (int k = 0; k < D; ++k) v[k] = (me && (i >> 6) == (uint32_t)k) ? x : v[k];
+  }
 }
 // Open a hole at directory position i (entries i.. move up by one; the last
 // one falls off) and put x there.
@@ -129,8 +154,8 @@ __device__ __forceinline__ void dir_erase(uint32_t (&v)[D], uint32_t i, uint32_t
 }
 
 // One table of sorted chunks of 8-byte entries (key, value): the key is a
-// block's end granule, the value its size or its record.  KEY64: sorted by
-// (value, key) instead (best fit's (size, end) keys).  MAXS: the directory
+// block's last granule, the value its size or its record.  KEY64: sorted by
+// (value, key) instead (best fit's keys).  MAXS: the directory
 // keeps each chunk's largest value (first and next fit: the largest size).
 template <bool KEY64, bool MAXS, int D>
 struct Hal {
@@ -176,7 +201,7 @@ struct Hal {
     sl = sl < NC ? sl : NC - 1u;
     const uint32_t lane = lane_id();
     u32x2 v;
-    if (sl < nl) {
+    if (likely(sl < nl)) {
       v = *(const HDA_LDS u32x2*)(lb + sl * CB + lane * 8u);
     } else {
       v = *(const HDA_GLOBAL u32x2*)(gb + (uint64_t)sl * CB + lane * 8u);
@@ -191,7 +216,7 @@ struct Hal {
     const uint32_t lane = lane_id();
     u32x2 v;
     v[0] = r.a; v[1] = r.s;
-    if (sl < nl) *(HDA_LDS u32x2*)(lb + sl * CB + lane * 8u) = v;
+    if (likely(sl < nl)) *(HDA_LDS u32x2*)(lb + sl * CB + lane * 8u) = v;
     else *(HDA_GLOBAL u32x2*)(gb + (uint64_t)sl * CB + lane * 8u) = v;
   }
   // field f (0 key, 1 value) of entry p, written by every lane
@@ -200,7 +225,7 @@ struct Hal {
     wave_sync();
     sl = sl < NC ? sl : NC - 1u;
     const uint32_t off = (p & 63u) * 8u + (f & 1u) * 4u;
-    if (sl < nl) *(HDA_LDS uint32_t*)(lb + sl * CB + off) = x;
+    if (likely(sl < nl)) *(HDA_LDS uint32_t*)(lb + sl * CB + off) = x;
     else *(HDA_GLOBAL uint32_t*)(gb + (uint64_t)sl * CB + off) = x;
   }
   __device__ __forceinline__ void store_entry(uint32_t sl, uint32_t p, uint32_t a,
@@ -210,30 +235,24 @@ struct Hal {
     u32x2 v;
     v[0] = a; v[1] = s;
     const uint32_t off = (p & 63u) * 8u;
-    if (sl < nl) *(HDA_LDS u32x2*)(lb + sl * CB + off) = v;
+    if (likely(sl < nl)) *(HDA_LDS u32x2*)(lb + sl * CB + off) = v;
     else *(HDA_GLOBAL u32x2*)(gb + (uint64_t)sl * CB + off) = v;
   }
 
   // ---- keys ----
-  // Lanes whose key (r1, r0) is <= (k1, k0) (strict: <); keyed by r0 alone
-  // unless KEY64.  Each comparison is one ballot; they are combined on the
-  // scalar side.
+  // Lanes whose key (r1, r0) is below (k1, k0); keyed by r0 alone unless
+  // KEY64 (then as one 64-bit value: one vector compare).
   __device__ __forceinline__ static uint64_t key_ballot(uint32_t r1, uint32_t r0, uint32_t k1,
-                                                        uint32_t k0, bool strict) {
-    if constexpr (!KEY64) return strict ? ballot(r0 < k0) : ballot(r0 <= k0);
-    // (r1, r0) as one 64-bit value: one vector compare
-    const uint64_t r = ((uint64_t)r1 << 32) | r0, k = ((uint64_t)k1 << 32) | k0;
-    return strict ? ballot(r < k) : ballot(r <= k);
+                                                        uint32_t k0) {
+    if constexpr (!KEY64) return ballot(r0 < k0);
+    return ballot((((uint64_t)r1 << 32) | r0) < (((uint64_t)k1 << 32) | k0));
   }
-  // chunks whose first key is <= (k1, k0) (strict: <)
-  __device__ __forceinline__ uint32_t count_first(uint32_t k1, uint32_t k0, bool strict) const {
+  // chunks whose first key is below (k1, k0)
+  __device__ __forceinline__ uint32_t count_first(uint32_t k1, uint32_t k0) const {
     uint32_t n = 0;
 #pragma unroll
-    for (int k = 0; k < D; ++k) {
-      const uint32_t base = 64u * (uint32_t)k;
-      const uint64_t le = key_ballot(dk1[k], dk0[k], k1, k0, strict);
-      n += (uint32_t)__builtin_popcountll(le & lanes_below(nc > base ? nc - base : 0u));
-    }
+    for (int k = 0; k < D; ++k)
+      n += (uint32_t)__builtin_popcountll(key_ballot(dk1[k], dk0[k], k1, k0));
     return n;
   }
 
@@ -246,6 +265,23 @@ struct Hal {
     dir_put(dk0, ci, rdlane(r.a, 0));
     if (KEY64) dir_put(dk1, ci, rdlane(r.s, 0));
     if (MAXS) dir_put(dmx, ci, wave_max(r.s));
+  }
+
+  // the entry chunk ci starts with (written whether it changed or not: a
+  // test costs as much and a branch more)
+  __device__ __forceinline__ void first(uint32_t ci, uint32_t a, uint32_t s) {
+    dir_put(dk0, ci, a);
+    if (KEY64) dir_put(dk1, ci, s);
+  }
+  // A chunk's largest value when one of them has grown to s, or when one
+  // that was s is gone or smaller (row o is what is left): only the largest
+  // itself going takes a reduction over the row.
+  __device__ __forceinline__ void grow(uint32_t ci, uint32_t s) {
+    const uint32_t old = dir_get(dmx, ci);
+    dir_put(dmx, ci, old > s ? old : s);
+  }
+  __device__ __forceinline__ void shrink(uint32_t ci, uint32_t s, const Row& o) {
+    if (unlikely(s == dir_get(dmx, ci))) dir_put(dmx, ci, wave_max(o.s));
   }
 
   __device__ __forceinline__ uint32_t take_slot() {
@@ -306,10 +342,12 @@ struct Hal {
     const uint32_t n = count(ci), sl = slot(ci);
     // the row moved up one lane (lane 0: the sentinel)
     const Row up{wave_shr1(kNone, r.a), wave_shr1(kSentS, r.s)};
-    if (n < 64u) {
+    if (likely(n < 64u)) {
       const Row o = pick(lane < p, r, pick(lane == p, e, up));
       store(sl, o);
-      describe(ci, o, n + 1u);
+      dir_put(dct, ci, n + 1u);
+      first(ci, rdlane(o.a, 0), KEY64 ? rdlane(o.s, 0) : 0u);
+      if (MAXS) grow(ci, e.s);
       return;
     }
     // split: the 65 entries c[0..64] become 33 here and 32 in a new chunk
@@ -341,9 +379,11 @@ struct Hal {
     // the row moved down one lane (lane 63: the sentinel)
     const Row down{wave_shl1(kNone, r.a), wave_shl1(kSentS, r.s)};
     const Row o = pick(lane >= p, down, r);
-    if (n >= 32u || nc == 1u) {
+    if (likely(n >= 32u || nc == 1u)) {
       store(sl, o);
-      describe(ci, o, n);
+      dir_put(dct, ci, n);
+      first(ci, rdlane(o.a, 0), KEY64 ? rdlane(o.s, 0) : 0u);
+      if (MAXS) shrink(ci, rdlane(r.s, p), o);
       return;
     }
     // join with the next chunk (or the previous one for the last chunk)
@@ -384,40 +424,29 @@ struct Hal {
     describe(hi, m1, b);
   }
 
-  // The last chunk whose first key is <= (k1, k0): ci (kNone if every chunk
-  // starts above it), its row, and p = the position of the last entry <= the
-  // key in it.
+  // Where key (k1, k0) belongs: chunk ci (the last one starting below it,
+  // else the first), its row, and the number q of its entries below the key.
+  // An entry equal to the key is at position q, or starts the next chunk; to
+  // find it, ask for the key one above it: it is then at q - 1.
   __device__ __forceinline__ void locate(uint32_t k1, uint32_t k0, uint32_t& ci, Row& r,
-                                         uint32_t& p) const {
-    const uint32_t c = count_first(k1, k0, false);
-    if (c == 0u) { ci = kNone; p = kNone; return; }
-    ci = c - 1u;
+                                         uint32_t& q) const {
+    const uint32_t c = count_first(k1, k0);
+    ci = c != 0u ? c - 1u : 0u;
     r = load(slot(ci));
-    const uint32_t n = count(ci);
-    p = (uint32_t)__builtin_popcountll(key_ballot(r.s, r.a, k1, k0, false) & lanes_below(n)) - 1u;
-  }
-  // Where a new key goes: chunk ci (the last one starting below it, else
-  // the first), its row, and the position of the first entry above it.
-  __device__ __forceinline__ void insert_pos(uint32_t k1, uint32_t k0, uint32_t& ci, Row& r,
-                                             uint32_t& p) const {
-    const uint32_t c = count_first(k1, k0, true);
-    ci = c == 0u ? 0u : c - 1u;
-    r = load(slot(ci));
-    const uint32_t n = count(ci);
-    p = (uint32_t)__builtin_popcountll(key_ballot(r.s, r.a, k1, k0, true) & lanes_below(n));
+    q = (uint32_t)__builtin_popcountll(key_ballot(r.s, r.a, k1, k0));
   }
   // (value, key) tables: insert and remove one key
   __device__ __forceinline__ void insert_key(uint32_t a, uint32_t s) {
-    uint32_t ci, p;
+    uint32_t ci, q;
     Row r;
-    insert_pos(s, a, ci, r, p);
-    insert_at(ci, p, r, Row{a, s});
+    locate(s, a, ci, r, q);
+    insert_at(ci, q, r, Row{a, s});
   }
   __device__ __forceinline__ void erase_key(uint32_t a, uint32_t s) {
-    uint32_t ci, p;
+    uint32_t ci, q;
     Row r;
-    locate(s, a, ci, r, p);
-    erase_at(ci, p, r);
+    locate(s, a + 1u, ci, r, q);
+    erase_at(ci, q - 1u, r);
   }
   // first chunk at or after `from` whose largest value is >= sg (MAXS
   // tables), or kNone
@@ -425,9 +454,8 @@ struct Hal {
     uint32_t c = kNone;
 #pragma unroll
     for (int k = D - 1; k >= 0; --k) {
-      const uint32_t base = 64u * (uint32_t)k;
-      const uint64_t m = ballot(dmx[k] >= sg) & lanes_below(nc > base ? nc - base : 0u) &
-                         ~lanes_below(from > base ? from - base : 0u);
+      const uint32_t base = 64u * (uint32_t)k;  // (unused lanes hold 0)
+      const uint64_t m = ballot(dmx[k] >= sg) & ~lanes_below(from > base ? from - base : 0u);
       c = m != 0ull ? 64u * (uint32_t)k + ctz64(m) : c;
     }
     return c;
@@ -551,6 +579,7 @@ struct OrdHeap {
   uint64_t bm;          // segregated fit: class bitmap; TLSF: first-level bitmap
   uint32_t slb;         // TLSF: lane fl = bitmap of the 32 sub-classes of level fl
   uint32_t frl, frh;    // free records: lane l, bit b <=> record 64 l + b (low, high word)
+  uint32_t spare;       // one more free record, or kNone
 
   __device__ __forceinline__ OrdHeap(const OrdMem& mem, const HeapRegs& h, uint32_t cap_free,
                                      uint32_t cap_live)
@@ -558,15 +587,10 @@ struct OrdHeap {
         capF(cap_free < kOrdMaxFree ? cap_free : kOrdMaxFree), capL(cap_live) {}
 
   // ---- live table ----
-  // (every lane reads the same entry; the halves are made wave-uniform so
-  // that what is computed from them stays scalar)
-  __device__ __forceinline__ Ent lget(uint32_t i) const {
-    const Ent e = lraw(i);
-    return mk_ent(uniform(ent_a(e)), uniform(ent_s(e)));
-  }
+  // (every lane reads the same entry)
   __device__ __forceinline__ Ent lraw(uint32_t i) const {
     wave_sync();
-    if (i < m.ll_n) return m.ll[i];
+    if (likely(i < m.ll_n)) return m.ll[i];
     const Ent e = m.gl[i];
     settle((uint32_t)e);
     settle((uint32_t)(e >> 32));
@@ -574,7 +598,7 @@ struct OrdHeap {
   }
   __device__ __forceinline__ void lset(uint32_t i, Ent e) const {
     wave_sync();
-    if (i < m.ll_n) m.ll[i] = e; else m.gl[i] = e;  // every lane, same value
+    if (likely(i < m.ll_n)) m.ll[i] = e; else m.gl[i] = e;  // every lane, same value
   }
   __device__ __forceinline__ Ent lchunk(uint32_t base) const {  // base: multiple of 64
     wave_sync();
@@ -591,7 +615,7 @@ struct OrdHeap {
     wave_sync();
     i = i < kOrdMaxFree ? i : kOrdMaxFree - 1u;
     u32x4 v;
-    if (i < m.rec_n) {
+    if (likely(i < m.rec_n)) {
       v = m.rec_l[i];
     } else {
       v = m.rec_g[i];
@@ -609,16 +633,22 @@ struct OrdHeap {
     i = i < kOrdMaxFree ? i : kOrdMaxFree - 1u;
     u32x4 v;
     v[0] = a; v[1] = s; v[2] = nx; v[3] = pv;
-    if (i < m.rec_n) m.rec_l[i] = v; else m.rec_g[i] = v;
+    if (likely(i < m.rec_n)) m.rec_l[i] = v; else m.rec_g[i] = v;
   }
   // one field (2 next, 3 prev) of record i
   __device__ __forceinline__ void rec_link(uint32_t i, uint32_t f, uint32_t x) const {
     wave_sync();
     i = i < kOrdMaxFree ? i : kOrdMaxFree - 1u;
-    if (i < m.rec_n) ((HDA_LDS uint32_t*)(m.rec_l + i))[f & 3u] = x;
+    if (likely(i < m.rec_n)) ((HDA_LDS uint32_t*)(m.rec_l + i))[f & 3u] = x;
     else ((HDA_GLOBAL uint32_t*)(m.rec_g + i))[f & 3u] = x;
   }
+  // (the record given back last is taken first: spare)
   __device__ __forceinline__ uint32_t rec_take() {
+    const uint32_t top = spare;
+    if (likely(top != kNone)) {
+      spare = kNone;
+      return top;
+    }
     const uint64_t m1 = ballot((frl | frh) != 0u);
     const uint32_t l = m1 != 0ull ? ctz64(m1) : 63u;
     const uint32_t wl = rdlane(frl, l), wh = rdlane(frh, l);
@@ -630,6 +660,10 @@ struct OrdHeap {
     return 64u * l + b;
   }
   __device__ __forceinline__ void rec_give(uint32_t i) {
+    const uint32_t old = spare;
+    spare = i;
+    if (likely(old == kNone)) return;
+    i = old;
     const bool me = lane_id() == (i >> 6);
     const uint32_t b = i & 63u;
     frl = me && b < 32u ? frl | (1u << b) : frl;
@@ -699,7 +733,7 @@ struct OrdHeap {
   __device__ __forceinline__ void init() {
     ta.init(m.ta_l, m.ta_g, m.ta_n);
     F = 1; L = 0; rover = 0;
-    hd = kNone; bm = 0ull; slb = 0u;
+    hd = kNone; bm = 0ull; slb = 0u; spare = kNone;
     if constexpr (kSeg) {
       // records 0 .. capF - 1 are free, then record 0 takes the arena
       const uint32_t base = 64u * lane_id();
@@ -714,31 +748,31 @@ struct OrdHeap {
       }
       const uint32_t r0 = rec_take();
       push(r0, 0u, ag);
-      ta.start(ag, r0);
+      ta.start(ag - 1u, r0);
     } else {
       frl = frh = 0u;
-      ta.start(ag, ag);
+      ta.start(ag - 1u, ag);
     }
     if constexpr (kKeys) {
       tb.init(m.tb_l, m.tb_g, m.tb_n);
-      tb.start(ag, ag);
+      tb.start(ag - 1u, ag);
     }
   }
 
   // First and next fit: the block at position p of chunk ci (row r current,
-  // key e = its end, value s = its size) gives sg granules from its low end.
+  // key e = its last granule, value s = its size) gives sg granules from its
+  // low end.
   __device__ __forceinline__ int64_t commit_fit(uint32_t ci, uint32_t p, const Row& r,
                                                 uint32_t e, uint32_t s, uint32_t sg) {
-    const uint32_t a = e - s;
-    if (s > sg) {
+    const uint32_t a = e - s + 1u;
+    live_push(a, sg);
+    if (likely(s > sg)) {
       ta.store_field(ta.slot(ci), p, 1u, s - sg);  // the end stays
-      if (kMax) dir_put(ta.dmx, ci, wave_max(TA::with(r, p, e, s - sg).s));
+      if (kMax) ta.shrink(ci, s, TA::with(r, p, e, s - sg));
     } else {
       ta.erase_at(ci, p, r);
       --F;
     }
-    lset(L, mk_ent(a, sg));
-    ++L;
     if (ALGO == kNextFit) rover = a + sg;
     return (int64_t)(uint64_t)a;
   }
@@ -830,8 +864,8 @@ struct OrdHeap {
       if (v) {
         // a record's number is its rank by key: a class's blocks are
         // numbered one after another from the head
-        place(m.ta_g, ra, n, e, kSeg ? rb : s);
-        if constexpr (kKeys) place(m.tb_g, rb, n, e, s);
+        place(m.ta_g, ra, n, e - 1u, kSeg ? rb : s);
+        if constexpr (kKeys) place(m.tb_g, rb, n, e - 1u, s);
         if constexpr (kSeg) {
           u32x4 r;
           r[0] = a; r[1] = s;
@@ -844,7 +878,7 @@ struct OrdHeap {
     wave_order();
     build(ta, n);
     if constexpr (kKeys) build(tb, n);
-    hd = kNone; bm = 0ull; slb = 0u; frl = frh = 0u;
+    hd = kNone; bm = 0ull; slb = 0u; frl = frh = 0u; spare = kNone;
     if constexpr (kSeg) {
       // free record numbers: F .. capF - 1
       const uint32_t b0 = 64u * lane;
@@ -913,7 +947,7 @@ struct OrdHeap {
     widen(ta, o.ta);
     if constexpr (kKeys) widen(tb, o.tb);
     F = o.F; L = o.L; rover = o.rover;
-    hd = o.hd; bm = o.bm; slb = o.slb; frl = o.frl; frh = o.frh;
+    hd = o.hd; bm = o.bm; slb = o.slb; frl = o.frl; frh = o.frh; spare = o.spare;
   }
   template <typename T2, typename T1>
   __device__ __forceinline__ static void widen(T2& t, const T1& o) {
@@ -933,7 +967,7 @@ struct OrdHeap {
     if (CHK && full_dir()) return kOverflow;
     if constexpr (ALGO == kFirstFit) {
       const uint32_t ci = ta.first_fit_chunk(sg, 0u);
-      if (ci == kNone) return kFail;
+      if (ci == kNone) return fail();
       const Row r = ta.load(ta.slot(ci));
       const uint32_t p = ctz64(ballot(r.s >= sg));
       const uint32_t e = rdlane(r.a, p), s = rdlane(r.s, p);
@@ -943,34 +977,31 @@ struct OrdHeap {
       // the search starts at the first block ending past the rover (R9-R11)
       // and runs on cyclically: the rest of that chunk, the later chunks,
       // then from the first chunk
-      uint32_t ci0, p0;
-      Row r0;
-      ta.locate(0u, rover, ci0, r0, p0);
-      uint32_t ci = kNone, p = 0;
+      uint32_t ci, q0;
       Row r;
-      bool found = false;
-      if (ci0 != kNone) {
-        const uint64_t fit = ballot(r0.s >= sg) & lanes_below(ta.count(ci0)) & ~lanes_below(p0 + 1u);
-        if (fit != 0ull) { ci = ci0; p = ctz64(fit); r = r0; found = true; }
-      }
-      if (!found) {
-        const uint32_t c1 = ta.first_fit_chunk(sg, ci0 == kNone ? 0u : ci0 + 1u);
+      ta.locate(0u, rover, ci, r, q0);
+      uint32_t p;
+      const uint64_t fit = ballot(r.s >= sg) & ~lanes_below(q0);
+      if (likely(fit != 0ull)) {
+        p = ctz64(fit);
+      } else {
+        const uint32_t c1 = ta.first_fit_chunk(sg, ci + 1u);
         const uint32_t c2 = c1 != kNone ? c1 : ta.first_fit_chunk(sg, 0u);
-        if (c2 == kNone) return kFail;
+        if (c2 == kNone) return fail();
+        if (c2 != ci) r = ta.load(ta.slot(c2));
         ci = c2;
-        r = c2 == ci0 ? r0 : ta.load(ta.slot(c2));
-        p = ctz64(ballot(r.s >= sg) & lanes_below(ta.count(c2)));
+        p = ctz64(ballot(r.s >= sg));
       }
       const uint32_t e = rdlane(r.a, p), s = rdlane(r.s, p);
       if (CHK && L >= capL) return kENoMeta;
       return commit_fit(ci, p, r, e, s, sg);
     } else if constexpr (ALGO == kBestFit) {
-      // smallest key (size, end) at or above (sg, 0)
+      // smallest key (size, last granule) at or above (sg, 0)
       uint32_t ci, p;
       typename TB::Row r;
-      tb.insert_pos(sg, 0u, ci, r, p);
-      if (p >= tb.count(ci)) {
-        if (ci + 1u >= tb.nc) return kFail;
+      tb.locate(sg, 0u, ci, r, p);
+      if (unlikely(p >= tb.count(ci))) {
+        if (ci + 1u >= tb.nc) return fail();
         ci = ci + 1u;
         r = tb.load(tb.slot(ci));
         p = 0u;
@@ -981,34 +1012,34 @@ struct OrdHeap {
       // table's updates do not touch it, and its load then overlaps them
       uint32_t cj, q;
       Row ra;
-      ta.locate(0u, e, cj, ra, q);
+      ta.locate(0u, e + 1u, cj, ra, q);
       tb.erase_at(ci, p, r);
-      if (s > sg) tb.insert_key(e, s - sg);
-      return commit_fit(cj, q, ra, e, s, sg);
+      if (likely(s > sg)) tb.insert_key(e, s - sg);
+      return commit_fit(cj, q - 1u, ra, e, s, sg);
     } else {
       // class of the first non-empty list at or above the request's
       uint32_t c;
       if constexpr (ALGO == kTlsf) {
-        if (kreq >= kTlsfClasses) return kFail;
         const uint32_t fl = kreq >> 5, sl = kreq & 31u;
         const uint32_t m2 = rdlane(slb, fl) & (~0u << sl);
         if (m2 != 0u) {
           c = (fl << 5) | (uint32_t)__builtin_ctz(m2);
         } else {
           const uint64_t m1 = fl < 63u ? bm & (~0ull << (fl + 1u)) : 0ull;
-          if (m1 == 0ull) return kFail;
+          if (m1 == 0ull) return fail();
           const uint32_t f2 = ctz64(m1);
           c = (f2 << 5) | (uint32_t)__builtin_ctz(rdlane(slb, f2));
         }
       } else {
-        if (kreq >= 64u) return kFail;
+        // (a request no larger than the arena has a class below 64)
         const uint64_t mk = bm & (~0ull << kreq);
-        if (mk == 0ull) return kFail;
+        if (mk == 0ull) return fail();
         c = ctz64(mk);
       }
       const uint32_t i = head(c);
       const Rec b = rec(i);
       if (CHK && L >= capL) return kENoMeta;
+      live_push(b.a, sg);
       // pop the head (Alg. 4), keeping the lists' invariants (R20)
       set_head(c, b.nx);
       if (b.nx == kNone) bit_clear(c); else rec_link(b.nx, 3u, kNone);
@@ -1017,15 +1048,13 @@ struct OrdHeap {
         // its class (Alg. 4)
         push(i, b.a + sg, b.s - sg);
       } else {
-        uint32_t ci, p;
+        uint32_t ci, q;
         Row r;
-        ta.locate(0u, b.a + b.s, ci, r, p);
-        ta.erase_at(ci, p, r);
+        ta.locate(0u, b.a + b.s, ci, r, q);
+        ta.erase_at(ci, q - 1u, r);
         rec_give(i);
         --F;
       }
-      lset(L, mk_ent(b.a, sg));
-      ++L;
       return (int64_t)(uint64_t)b.a;
     }
   }
@@ -1035,49 +1064,52 @@ struct OrdHeap {
   // entry would exceed the capacity.
   template <bool CHK = true>
   __device__ __forceinline__ bool release(uint32_t x, uint32_t sz) {
-    const uint32_t lane = lane_id();
     const uint32_t xe = x + sz;
-    // the block ending at x (an exact key) and the block after x (the next
-    // entry, starting at xe if it borders)
-    uint32_t ci, p;
+    // the block whose last granule is x - 1 (an exact key) and the block
+    // after x (the next entry, starting at xe if it borders)
+    uint32_t ci, q;
     Row r;
-    ta.locate(0u, x, ci, r, p);
-    const bool hasL = ci != kNone && rdlane(r.a, p) == x;
-    const uint32_t vl = ci != kNone ? rdlane(r.s, p) : 0u;  // size or record
-    // the entry after position p of chunk ci (ci = kNone: the first entry)
-    uint32_t rci = kNone, rp = 0;
+    ta.locate(0u, x, ci, r, q);
+    // best fit: where the freed part's own key goes if nothing merges, its
+    // load beside the address table's
+    uint32_t ck = 0, k = 0;
+    typename TB::Row rk{0u, 0u};
+    if constexpr (kKeys) tb.locate(sz, xe - 1u, ck, rk, k);
+    const uint32_t p = q - 1u;
+    const bool hasL = q != 0u && rdlane(r.a, p) + 1u == x;
+    const uint32_t vl = rdlane(r.s, p);  // size or record (hasL)
+    // the entry at position q, or the first one of the next chunk
+    uint32_t rci = ci, rp = q;
     Row rr = r;
-    if (ci != kNone && p + 1u < ta.count(ci)) {
-      rci = ci; rp = p + 1u;
-    } else {
-      const uint32_t nci = ci == kNone ? 0u : ci + 1u;
-      if (nci < ta.nc && ta.count(nci) != 0u) {
-        rci = nci; rp = 0u;
-        rr = ta.load(ta.slot(nci));
+    bool next = true;
+    if (unlikely(q >= ta.count(ci))) {
+      next = ci + 1u < ta.nc;
+      if (next) {
+        rci = ci + 1u; rp = 0u;
+        rr = ta.load(ta.slot(rci));
       }
     }
-    const uint32_t er = rci != kNone ? rdlane(rr.a, rp) : 0u;
-    const uint32_t vr = rci != kNone ? rdlane(rr.s, rp) : 0u;
+    const uint32_t er = rdlane(rr.a, rp), vr = rdlane(rr.s, rp);
     uint32_t sl = 0, sr = 0;
     Rec bl{0, 0, kNone, kNone}, br{0, 0, kNone, kNone};
     bool hasR;
     if constexpr (kSeg) {
-      // both records are loaded before either is used
-      const u32x4 ql = rec_raw(hasL ? vl : 0u), qr = rec_raw(rci != kNone ? vr : 0u);
-      if (hasL) bl = rec_of(ql);
-      if (rci != kNone) br = rec_of(qr);
+      // the right record says whether its block borders
+      const u32x4 qr = rec_raw(next ? vr : 0u);
+      if (hasL) bl = rec(vl);
+      br = rec_of(qr);
       sl = bl.s;
       sr = br.s;
-      hasR = rci != kNone && br.a == xe;
+      hasR = next && br.a == xe;
     } else {
       sl = vl;
       sr = vr;
-      hasR = rci != kNone && er - vr == xe;
+      hasR = next && er + 1u - vr == xe;
     }
     if (CHK && !hasL && !hasR && F >= capF) return false;
     const uint32_t ma = hasL ? x - sl : x;
     const uint32_t ms = (hasL ? sl : 0u) + sz + (hasR ? sr : 0u);
-    const uint32_t me = hasR ? er : xe;  // end of the merged block
+    const uint32_t me = hasR ? er : xe - 1u;  // last granule of the merged block
     if constexpr (kSeg) {
       // unlink the free neighbours, then push the merged block (R21)
       if (hasL) {
@@ -1090,9 +1122,10 @@ struct OrdHeap {
       if (hasR) unlink(sr, br.nx, br.pv);
     }
     if constexpr (kKeys) {
-      if (hasL) tb.erase_key(x, sl);
+      if (hasL) tb.erase_key(x - 1u, sl);
       if (hasR) tb.erase_key(er, sr);
-      tb.insert_key(me, ms);
+      if (hasL || hasR) tb.insert_key(me, ms);
+      else tb.insert_at(ck, k, rk, typename TB::Row{me, ms});
     }
     if (hasL && hasR) {
       // the right block's entry keeps its end and takes the merged block;
@@ -1103,16 +1136,16 @@ struct OrdHeap {
       } else {
         ta.store_field(ta.slot(rci), rp, 1u, ms);
         if (rci == ci) r = TA::with(r, rp, er, ms);  // the row erase_at shifts
-        else if (kMax) dir_put(ta.dmx, rci, wave_max(TA::with(rr, rp, er, ms).s));
+        if (kMax) ta.grow(rci, ms);
       }
       ta.erase_at(ci, p, r);
       --F;
     } else if (hasL) {
-      // the left block's entry: end x -> xe (its place does not change)
+      // the left block's entry ends later now (its place does not change)
       const uint32_t v = kSeg ? vl : ms;
-      ta.store_entry(ta.slot(ci), p, xe, v);
-      if (p == 0u) dir_put(ta.dk0, ci, xe);
-      if (kMax) dir_put(ta.dmx, ci, wave_max(TA::with(r, p, xe, ms).s));
+      ta.store_entry(ta.slot(ci), p, me, v);
+      if (p == 0u) dir_put(ta.dk0, ci, me);
+      if (kMax) ta.grow(ci, ms);
       if constexpr (kSeg) push(vl, ma, ms);
     } else if (hasR) {
       // the right block grows downwards: its end and its entry stay
@@ -1120,45 +1153,44 @@ struct OrdHeap {
         push(vr, ma, ms);
       } else {
         ta.store_field(ta.slot(rci), rp, 1u, ms);
-        if (kMax) dir_put(ta.dmx, rci, wave_max(TA::with(rr, rp, er, ms).s));
+        if (kMax) ta.grow(rci, ms);
       }
     } else {
-      // a new entry right after position p (ci = kNone: first of chunk 0)
+      // a new entry at position q
       uint32_t v = sz;
       if constexpr (kSeg) {
         v = rec_take();
         push(v, x, sz);
       }
-      const uint32_t ic = ci == kNone ? 0u : ci, ip = ci == kNone ? 0u : p + 1u;
-      const Row ir = ci == kNone ? (rci == 0u ? rr : ta.load(ta.slot(0u))) : r;
-      ta.insert_at(ic, ip, ir, Row{xe, v});
+      ta.insert_at(ci, q, r, Row{me, v});
       ++F;
     }
-    (void)lane;
     return true;
   }
 
   // Free live entry idx except its first floor(cut * size / 2^31) granules
   // (partial deallocation, sequential fits; cut < 2^31).  Returns the first
   // granule of the released part or kENoMeta.
+  // v0, w0: the victim and the last live entry, as loaded.
   template <bool CHK = true>
-  __device__ __forceinline__ int64_t free_index(uint32_t idx, uint32_t cut) {
-    if (CHK && full_dir()) return kOverflow;
-    const uint32_t last = L - 1u;
-    // both entries are loaded before either is used, so their latencies
-    // overlap
-    const Ent v0 = lraw(idx), w0 = lraw(last);
+  __device__ __forceinline__ int64_t free_index(uint32_t idx, Ent v0, Ent w0, uint32_t cut) {
     const Ent v = mk_ent(uniform(ent_a(v0)), uniform(ent_s(v0)));
-    const Ent w = mk_ent(uniform(ent_a(w0)), uniform(ent_s(w0)));
     const uint32_t bx = ent_a(v), bsz = ent_s(v);
     const uint32_t t = (kSeg || cut == 0u) ? 0u : (uint32_t)(((uint64_t)cut * bsz) >> 31);
     const uint32_t x = bx + t, sz = bsz - t;
-    if (!release<CHK>(x, sz)) return kENoMeta;
+    // the live table does not depend on the free one: without checks it is
+    // brought up to date first, and the next request's victim is on its way
+    // while this one's part is released
+    if (CHK && !release<CHK>(x, sz)) return kENoMeta;
     if (t != 0u) {
       lset(idx, mk_ent(bx, t));
     } else {
-      lset(idx, w);
-      L = last;
+      lset(idx, w0);
+      --L;
+    }
+    if (!CHK) {
+      look_ahead();
+      release<CHK>(x, sz);
     }
     return (int64_t)(uint64_t)x;
   }
@@ -1166,7 +1198,41 @@ struct OrdHeap {
   template <bool CHK = true>
   __device__ __forceinline__ int64_t free_draw(uint32_t r, uint32_t cut) {
     if (CHK && L == 0u) return kFail;
-    return free_index<CHK>((uint32_t)(((uint64_t)r * (uint64_t)L) >> 32), cut);
+    if (CHK && full_dir()) return kOverflow;
+    const uint32_t idx = (uint32_t)(((uint64_t)r * (uint64_t)L) >> 32);
+    if constexpr (CHK) {
+      const Ent v0 = lraw(idx), w0 = lraw(L - 1u);  // both loaded before either is used
+      return free_index<CHK>(idx, v0, w0, cut);
+    } else {
+      return free_index<CHK>(idx, nv, nw, cut);
+    }
+  }
+
+  // The victim of the next request, if that is a free, and the last live
+  // entry are loaded as soon as the live table is as that request will find
+  // it (blocks without checks): their latency, which nothing else hides from
+  // a lone wave, then overlaps the rest of the current request.
+  uint32_t nr;       // the next request's draw
+  bool nfree;        // it is a free
+  Ent nv, nw;        // its victim, the last live entry
+  __device__ __forceinline__ void next_request(bool is_free, uint32_t draw) {
+    nfree = is_free;
+    nr = draw;
+  }
+  __device__ __forceinline__ void look_ahead() {
+    if (nfree) {
+      nv = lraw((uint32_t)(((uint64_t)nr * (uint64_t)L) >> 32));
+      nw = lraw(L != 0u ? L - 1u : 0u);
+    }
+  }
+  __device__ __forceinline__ int64_t fail() {  // nothing fits
+    look_ahead();
+    return kFail;
+  }
+  __device__ __forceinline__ void live_push(uint32_t a, uint32_t sg) {
+    lset(L, mk_ent(a, sg));
+    ++L;
+    look_ahead();
   }
 
   // Whether the next n requests can skip the directory and capacity checks:
@@ -1197,7 +1263,7 @@ struct OrdHeap {
     for (uint32_t ci = 0; ci < ta.nc; ++ci) {
       const Row r = ta.load(ta.slot(ci));
       const uint32_t n = ta.count(ci);
-      uint32_t a = r.a - r.s, s = r.s;
+      uint32_t a = r.a + 1u - r.s, s = r.s;
       if constexpr (kSeg) {
         // this lane's record (lanes past the chunk read record 0, unused)
         wave_sync();

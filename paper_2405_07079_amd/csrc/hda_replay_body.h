@@ -85,6 +85,16 @@ struct UncheckedBlocks<OrdHeap<A, D>> {
   static constexpr bool value = true;
 };
 
+// Whether Core loads the next request's victim while the current one runs.
+template <typename Core>
+struct LooksAhead {
+  static constexpr bool value = false;
+};
+template <int A, int D>
+struct LooksAhead<OrdHeap<A, D>> {
+  static constexpr bool value = true;
+};
+
 // Requests j < n of one block of 64 on core w: lane j of w0 holds request
 // j's draw (free) or size in granules (allocation, 0 = larger than the
 // arena), lane j of w1 its byte class (segregated fit) or its cut (free,
@@ -102,8 +112,15 @@ __device__ __forceinline__ uint32_t run_block(Core& w, uint32_t n, uint32_t w0, 
                                               int32_t& st) {
   uint32_t done = n, olo = 0, ohi = 0;
   uint64_t frees = mfree;  // bit 0: the current request
+  if constexpr (UNCHK && LooksAhead<Core>::value) {  // (n >= 1)
+    w.next_request((uint32_t)frees & 1u, rdlane(w0, 0u));
+    w.look_ahead();
+  }
   for (uint32_t j = 0; j < n; ++j, frees >>= 1) {
     const uint32_t v0 = rdlane(w0, j);
+    // (past the block's end: no request, nothing is loaded)
+    if constexpr (UNCHK && LooksAhead<Core>::value)
+      w.next_request(keep_scalar((uint32_t)frees) & 2u, rdlane(w0, j + 1u));
     int64_t r;
     if (keep_scalar((uint32_t)frees) & 1u) {
       if constexpr (UNCHK) r = w.template free_draw<false>(v0, CUT ? rdlane(w1, j) : 0u);
