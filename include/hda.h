@@ -125,7 +125,8 @@ int hda_set_device_allocator(hda_dev_alloc_fn alloc, hda_dev_free_fn release, vo
  * 64*reg_free free-table entries are held in vector registers (reg_free = 1,
  * 2 or 4; 0 = 2); the rest of the free table and the whole live table share
  * one LDS pool per heap of lds_free * 16 + lds_live * 8 bytes (defaults 128
- * and 1024: 10 KiB), free entries from its start and live entries from its
+ * and 1024: 10 KiB; 2, 4 or 6 times that when so few heaps are in the batch
+ * that a CU holds 8, 4 or 2 of them), free entries from its start and live entries from its
  * end.  A heap whose tables outgrow the pool before reaching meta_free /
  * meta_live moves them, mid-trace, to the ordered core (pools of 10 KiB or
  * more, meta_free up to 4,096, and a workspace that holds its slots; else to
@@ -136,7 +137,8 @@ int hda_set_device_allocator(hda_dev_alloc_fn alloc, hda_dev_free_fn release, vo
  * (the live table is never held in registers).  0 = default for every
  * field; -1 = none of that storage.  Any other value is E_INVAL. */
 typedef struct hda_tuning {
-  int32_t heaps_per_group; /* waves (= heaps in flight) per workgroup (1..16)  */
+  int32_t heaps_per_group; /* waves (= heaps in flight) per workgroup (1..16;
+                              0 = 4, or 1 or 2 for batches of few heaps)       */
   int32_t reg_free;        /* free-table 64-entry chunks in registers          */
   int32_t reg_live;        /* live-table 64-entry chunks in registers          */
   int32_t lds_free;        /* free-table entries in LDS per heap (mult. of 64) */

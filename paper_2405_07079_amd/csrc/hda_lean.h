@@ -120,6 +120,7 @@ struct LeanHeap {
   static constexpr bool kGranules = true;  // alloc / free_draw return granules
   uint32_t F, L, rover, clock;
   uint32_t hint;                  // next fit, bitmask: the entry last cut (it may have moved)
+  uint32_t max_free = kNone;      // hand the heap over past this many free blocks
   uint32_t capF, capL;            // the caller's capacities (E_NOMETA past them)
   uint32_t live_room;             // live entries the pool holds beside the current free chunks
 

@@ -52,6 +52,7 @@ struct ReplayParams {
   // (ord_spill_bytes), or null
   uint8_t* ord_spill;
   uint64_t ord_spill_stride;
+  int lean_early;          // a heap goes there once scans cost more (lean_max_free)
 };
 
 // Validate heap parameters; on success fill the uniform heap registers.
@@ -82,6 +83,16 @@ struct UncheckedBlocks<LeanHeap<A, R>> {
 };
 template <int A, int D>
 struct UncheckedBlocks<OrdHeap<A, D>> {
+  static constexpr bool value = true;
+};
+
+// Whether Core may hand its heap over between two blocks of requests.
+template <typename Core>
+struct LeavesEarly {
+  static constexpr bool value = false;
+};
+template <int A, int R>
+struct LeavesEarly<LeanHeap<A, R>> {
   static constexpr bool value = true;
 };
 
@@ -166,6 +177,8 @@ __device__ __forceinline__ int64_t run_requests(const ReplayParams& p, Core& w, 
   const int64_t last = to - 1;
   int64_t nxt = to > from ? p.req[min<int64_t>(from + lane, last)] : 0;
   for (int64_t base = from; base < to; base += 64) {
+    if constexpr (LeavesEarly<Core>::value)
+      if (w.F > w.max_free) return base;
     const int64_t q = nxt;
     nxt = p.req[min<int64_t>(base + 64 + lane, last)];
     const bool is_free = q < 0;
@@ -298,6 +311,18 @@ struct LeanExit {
   uint32_t cnt;              // per lane (HeapRegs::cnt)
 };
 
+// Free blocks past which a heap with few waves beside it is better off on the
+// ordered core, whose request costs the same at any size, than scanning them
+// 64 at a time.  Where the two cross, with pools of 20 KiB or more (at most
+// two waves a SIMD): 500 first-fit heaps 9.4 ms without a limit, 7.9 / 7.3 /
+// 7.0 ms at 512 / 384 / 256; 1,000 next-fit heaps 6.1 ms, 5.3 / 5.2 / 5.3;
+// 200 segregated-fit heaps 20.6 ms, 16.7 / 16.8 / 17.1; one best-fit heap
+// (two sorted tables on the ordered core) 12.7 ms, 13.2 / 14.3 / 15.3.  With
+// four waves a SIMD the pools end before it matters (11.04 ms either way).
+__device__ __forceinline__ constexpr uint32_t lean_max_free(int algo) {
+  return algo == kFirstFit ? 256u : algo == kNextFit ? 384u : algo == kBestFit ? 1024u : 512u;
+}
+
 template <int ALGO>
 __device__ __forceinline__ OrdMem ord_spill_mem(const ReplayParams& p, HDA_LDS uint8_t* pool,
                                                 uint32_t pool_bytes, HDA_GLOBAL uint8_t* ord) {
@@ -320,6 +345,7 @@ __device__ __forceinline__ LeanExit lean_start(const ReplayParams& p, const Lean
   LeanHeap<ALGO, RF> w(lds, h, p.cap_free, p.cap_live);
   w.init();
   const int64_t b1 = p.req_off[heap + 1];
+  w.max_free = ord != nullptr && p.lean_early ? lean_max_free(ALGO) : kNone;
   x.pos = run_requests<ALGO>(p, w, p.req_off[heap], b1, w.shift, w.arena, x.st);
   if (x.pos == b1) {
     finish_heap(p, w, heap, x.st);
