@@ -120,13 +120,21 @@ struct LeanHeap {
   static constexpr bool kGranules = true;  // alloc / free_draw return granules
   uint32_t F, L, rover, clock;
   uint32_t hint;                  // next fit, bitmask: the entry last cut (it may have moved)
+  // The numbers of the first two LDS chunks in registers of their own: as
+  // constants the compiler puts them where a select needs the opposite
+  // comparison, and compares twice (best fit 1.8 %, segregated fit 0.7 %
+  // faster; first fit 0.5 % slower, which takes constants).
+  static constexpr bool kColdId = ALGO == kBestFit || kSeg;
+  uint32_t cold_id[2];
   uint32_t max_free = kNone;      // hand the heap over past this many free blocks
   uint32_t capF, capL;            // the caller's capacities (E_NOMETA past them)
   uint32_t live_room;             // live entries the pool holds beside the current free chunks
 
   __device__ __forceinline__ LeanHeap(const LeanLds& lds, const HeapRegs& h, uint32_t cap_free,
                                       uint32_t cap_live)
-      : m(lds), arena(h.arena), shift(h.shift), ag(h.ag), capF(cap_free), capL(cap_live) {}
+      : m(lds), arena(h.arena), shift(h.shift), ag(h.ag),
+        cold_id{opaque((uint32_t)RF), opaque((uint32_t)RF + 1u)}, capF(cap_free),
+        capL(cap_live) {}
 
   // ---- the LDS pool ----
   static constexpr uint32_t kRec = kSeg ? 16u : 8u;  // bytes per free entry in LDS
@@ -274,7 +282,8 @@ struct LeanHeap {
 #pragma unroll
     for (int u = 0; u < N; ++u) chunk_get(c + u, ea[u], ee[u], ek[u]);
 #pragma unroll
-    for (int u = 0; u < N; ++u) f(c + u, ea[u], ee[u], ek[u]);
+    for (int u = 0; u < N; ++u)
+      f(kColdId && N <= 2 && c == (uint32_t)RF ? cold_id[u & 1] : c + u, ea[u], ee[u], ek[u]);
   }
   template <typename Fn>
   __device__ __forceinline__ void scan(Fn&& f) {
