@@ -254,8 +254,9 @@ int hda_replay_per_heap(const hda_batch_desc *d, void *stream);
 int hda_replay_autotune(const hda_batch_desc *d, int32_t sample_heaps, void *stream,
                         hda_tuning *out);
 
-/* One hda_replay call on `d` recorded as a hipGraph (the classify kernel and
- * the replay kernel, captured on a private stream),
+/* One hda_replay call on `d` recorded as a hipGraph (the replay kernel, with
+ * the classify kernel before it when heaps outnumber the waves, captured on a
+ * private stream),
  * for callers that replay the same descriptor buffers repeatedly: each
  * hda_graph_launch re-runs the whole replay from the heaps' initial state on
  * `stream`, exactly as hda_replay would.  The descriptor's buffers must stay

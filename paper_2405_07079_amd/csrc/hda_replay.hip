@@ -104,11 +104,14 @@ __global__ void __launch_bounds__(1024) classify_kernel(ClassifyParams q) {
 
 // Persistent loop: waves pull list positions list_lo, list_lo + 1, ... from
 // p.queue until min(list_hi, the list's length) is reached; with use_queue =
-// 0 wave `slot` takes list entry first + slot.
+// 0 wave `slot` takes list entry first + slot (no list: heap first + slot).
 template <typename Fn>
 __device__ __forceinline__ void for_each_heap(const ReplayParams& p, uint64_t slot, Fn&& f) {
   if (!p.use_queue) {
-    if ((int64_t)slot < p.n_heaps) f((int64_t)p.list[p.first + (int64_t)slot]);
+    if ((int64_t)slot < p.n_heaps) {
+      const int64_t k = p.first + (int64_t)slot;
+      f(p.list ? (int64_t)p.list[k] : k);
+    }
     return;
   }
   const int64_t len = (int64_t)*p.count;
@@ -600,14 +603,27 @@ int classify(const hda_batch_desc* d, const Plan& pl, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? HDA_OK : HDA_E_DEVICE;
 }
 
-// Classify, then the persistent replay kernel, both on s.  With heaps for
+// The replay kernel alone when every heap has a wave of its own; else
+// classify, then the persistent replay kernel, both on s.  With heaps for
 // the ordered core, their launch follows classify on s and the other heaps'
 // launch runs beside it on the fork stream, joined back to s by an event.
 int enqueue(const hda_batch_desc* d, const Plan& pl, hipStream_t s) {
-  int rc = classify(d, pl, s);
-  if (rc != HDA_OK) return rc;
   ReplayParams p = replay_params(d, pl);
   const dim3 grid((uint32_t)pl.main.groups), block(64 * pl.main.W);
+  if (pl.heavy == 0 && pl.main.slots >= d->n_heaps) {
+    // A wave for every heap: wave i takes heap order[i], and rejects it if
+    // its parameters are invalid, so there is nothing to classify and no
+    // queue (the classify launch took 6 us for 48 heaps and 0.1 ms, one
+    // wave's walk over the order, for 4,096).
+    p.use_queue = 0;
+    p.list = d->order;
+    p.migrated = nullptr;
+    if (launch(pl.set->fn, grid, block, pl.main.lds_group, s, p) != hipSuccess)
+      return HDA_E_DEVICE;
+    return hipGetLastError() == hipSuccess ? HDA_OK : HDA_E_DEVICE;
+  }
+  int rc = classify(d, pl, s);
+  if (rc != HDA_OK) return rc;
   if (pl.heavy == 0) {
     if (launch(pl.set->fn, grid, block, pl.main.lds_group, s, p) != hipSuccess)
       return HDA_E_DEVICE;
