@@ -1,11 +1,15 @@
 // Single device-resident heaps driven call by call: heap_create / alloc /
 // free / state.  The heap's registers and tables live in device memory; each
 // call is one single-wave launch that loads the registers, runs one operation
-// of the same core as the batched replay, and stores them back.
+// of the same core as the batched replay, and stores them back.  The result
+// goes straight to the heap's word in pinned host memory, where the caller
+// looks for it: a copy back and a wait for the stream were more than half of
+// a call (22.8 -> 7.9 us for an allocation or a free on a 4 GiB heap).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -24,8 +28,12 @@ namespace {
 
 enum : int { kOpInit = 0, kOpAlloc = 1, kOpFree = 2, kOpDump = 3, kOpFreePartial = 4 };
 
+// What the host word holds until the call's result arrives (no result is it).
+constexpr int64_t kPending = INT64_MIN;
+
 template <int ALGO>
-__device__ void heap_call_t(HeapHdr* hd, int op, int64_t arg, int64_t* out, int64_t cap) {
+__device__ void heap_call_t(HeapHdr* hd, int op, int64_t arg, int64_t* dump, int64_t cap,
+                            int64_t* word) {
   const Cold c = heap_cold(hd);
   WaveHeap<ALGO, 0, 0> w(c, load_regs(hd), hd->cf, hd->cl);
   int64_t r = 0;
@@ -38,19 +46,21 @@ __device__ void heap_call_t(HeapHdr* hd, int op, int64_t arg, int64_t* out, int6
   } else if (op == kOpFreePartial) {
     r = w.free_partial(arg);
   } else {
-    r = w.dump(out + 1, cap - 1);
+    r = w.dump(dump, cap);
   }
+  if (lane_id() == 0)
+    __hip_atomic_store(word, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   store_regs(hd, w.h);
-  if (lane_id() == 0) out[0] = r;
 }
 
-__global__ void heap_call(HeapHdr* hd, int op, int64_t arg, int64_t* out, int64_t cap) {
+__global__ void heap_call(HeapHdr* hd, int op, int64_t arg, int64_t* dump, int64_t cap,
+                          int64_t* word) {
   switch (hd->algo) {
-    case kFirstFit: heap_call_t<kFirstFit>(hd, op, arg, out, cap); break;
-    case kNextFit: heap_call_t<kNextFit>(hd, op, arg, out, cap); break;
-    case kBestFit: heap_call_t<kBestFit>(hd, op, arg, out, cap); break;
-    case kSegFit: heap_call_t<kSegFit>(hd, op, arg, out, cap); break;
-    default: heap_call_t<kTlsf>(hd, op, arg, out, cap); break;
+    case kFirstFit: heap_call_t<kFirstFit>(hd, op, arg, dump, cap, word); break;
+    case kNextFit: heap_call_t<kNextFit>(hd, op, arg, dump, cap, word); break;
+    case kBestFit: heap_call_t<kBestFit>(hd, op, arg, dump, cap, word); break;
+    case kSegFit: heap_call_t<kSegFit>(hd, op, arg, dump, cap, word); break;
+    default: heap_call_t<kTlsf>(hd, op, arg, dump, cap, word); break;
   }
 }
 
@@ -69,6 +79,57 @@ struct Allocator {
 Allocator& allocator() {
   static Allocator a;
   return a;
+}
+
+// Result words in pinned host memory, one cache line each, 64 to a page: a
+// page is allocated when no word is free and given back when its last word
+// is, but for one empty page (making one takes 0.1 ms, which each heap would
+// pay).
+class WordPool {
+  struct Page {
+    uint8_t* host;
+    uint64_t used;  // bit i: word i is a heap's
+  };
+  std::mutex mu_;
+  std::vector<Page> pages_;
+
+ public:
+  int64_t* take() {
+    std::lock_guard<std::mutex> g(mu_);
+    for (Page& p : pages_)
+      if (~p.used) {
+        const int i = __builtin_ctzll(~p.used);
+        p.used |= 1ull << i;
+        return reinterpret_cast<int64_t*>(p.host + 64 * i);
+      }
+    void* host = nullptr;
+    if (hipHostMalloc(&host, 4096, hipHostMallocCoherent | hipHostMallocMapped |
+                                       hipHostMallocPortable) != hipSuccess)
+      return nullptr;
+    pages_.push_back({static_cast<uint8_t*>(host), 1ull});
+    return static_cast<int64_t*>(host);
+  }
+  void give(int64_t* w) {
+    std::lock_guard<std::mutex> g(mu_);
+    uint8_t* b = reinterpret_cast<uint8_t*>(w);
+    size_t empty = 0, at = pages_.size();
+    for (size_t k = 0; k < pages_.size(); ++k) {
+      Page& p = pages_[k];
+      if (b >= p.host && b < p.host + 4096) {
+        p.used &= ~(1ull << ((b - p.host) / 64));
+        if (p.used == 0) at = k;
+      }
+      empty += p.used == 0;
+    }
+    if (at < pages_.size() && empty > 1) {
+      (void)hipHostFree(pages_[at].host);
+      pages_.erase(pages_.begin() + (std::ptrdiff_t)at);
+    }
+  }
+};
+WordPool& words() {
+  static WordPool* w = new WordPool;  // (never destroyed: heaps may outlive statics)
+  return *w;
 }
 
 }  // namespace
@@ -113,8 +174,10 @@ hipStream_t lib_stream() {
 
 struct hda_heap {
   HeapHdr* dev = nullptr;      // header + tables (device)
-  int64_t* io = nullptr;       // device result / dump buffer
+  int64_t* io = nullptr;       // device dump buffer
   size_t io_words = 0;
+  int64_t* word = nullptr;     // the call's result (pinned host memory)
+  int64_t* dev_word = nullptr; // its device address
   size_t bytes = 0;            // metadata bytes charged to the budget
   hipStream_t stream = nullptr;  // the library's stream of the heap's device
   int algo = 0;
@@ -125,33 +188,49 @@ struct hda_heap {
 
 namespace {
 
+// Wait until the kernel has written the call's result: look for it for as
+// long as a call takes, then wait for the stream (other threads' calls on it
+// may come first) and report what that says.
+bool await_result(hda_heap* h, int64_t* r) {
+  constexpr auto kSpin = std::chrono::microseconds(100);
+  const auto began = std::chrono::steady_clock::now();
+  for (uint32_t n = 1;; ++n) {
+    *r = __atomic_load_n(h->word, __ATOMIC_ACQUIRE);
+    if (*r != kPending) return true;
+    __builtin_ia32_pause();
+    if (n % 64u == 0u && std::chrono::steady_clock::now() - began > kSpin) break;
+  }
+  if (hipStreamSynchronize(h->stream) != hipSuccess) return false;
+  *r = __atomic_load_n(h->word, __ATOMIC_ACQUIRE);
+  return *r != kPending;
+}
+
 int call(hda_heap* h, int op, int64_t arg, int64_t* result, int64_t* dump, size_t cap,
          size_t* len) {
   std::lock_guard<std::mutex> g(h->mu);
-  const size_t need_io = (op == kOpDump) ? cap + 1 : 1;
-  if (need_io > h->io_words) {
+  if (op == kOpDump && cap > h->io_words) {
     if (h->io) {
       (void)hipStreamSynchronize(h->stream);
       dev_free(h->io);
     }
     h->io = nullptr;
     h->io_words = 0;
-    h->io = static_cast<int64_t*>(dev_alloc(need_io * 8));
+    h->io = static_cast<int64_t*>(dev_alloc(cap * 8));
     if (!h->io) return HDA_E_DEVICE;
-    h->io_words = need_io;
+    h->io_words = cap;
   }
-  hipLaunchKernelGGL(heap_call, dim3(1), dim3(64), 0, h->stream, h->dev, op, arg, h->io,
-                     (int64_t)need_io);
+  __atomic_store_n(h->word, kPending, __ATOMIC_RELEASE);
+  hipLaunchKernelGGL(heap_call, dim3(1), dim3(64), 0, h->stream, h->dev, op, arg,
+                     op == kOpDump ? h->io : nullptr, op == kOpDump ? (int64_t)cap : 0,
+                     h->dev_word);
   if (hipGetLastError() != hipSuccess) return HDA_E_DEVICE;
   int64_t r = 0;
-  if (hipMemcpyAsync(&r, h->io, 8, hipMemcpyDeviceToHost, h->stream) != hipSuccess)
-    return HDA_E_DEVICE;
-  if (hipStreamSynchronize(h->stream) != hipSuccess) return HDA_E_DEVICE;
+  if (!await_result(h, &r)) return HDA_E_DEVICE;
   if (op == kOpDump) {
     *len = (size_t)r;
     if ((size_t)r > cap) return HDA_E_RANGE;
-    if (r > 0 && (hipMemcpyAsync(dump, h->io + 1, (size_t)r * 8, hipMemcpyDeviceToHost,
-                                 h->stream) != hipSuccess ||
+    if (r > 0 && (hipMemcpyAsync(dump, h->io, (size_t)r * 8, hipMemcpyDeviceToHost, h->stream) !=
+                      hipSuccess ||
                   hipStreamSynchronize(h->stream) != hipSuccess))
       return HDA_E_DEVICE;
     return HDA_OK;
@@ -318,8 +397,11 @@ int hda_heap_create(uint64_t arena_bytes, uint64_t align, int algo, uint32_t met
   h->align = align;
   h->cap = cap;
   h->stream = lib_stream();
-  h->dev = h->stream ? static_cast<HeapHdr*>(dev_alloc(bytes)) : nullptr;
+  if (h->stream && (h->word = words().take()) != nullptr &&
+      hipHostGetDevicePointer((void**)&h->dev_word, h->word, 0) == hipSuccess)
+    h->dev = static_cast<HeapHdr*>(dev_alloc(bytes));
   if (!h->dev) {
+    if (h->word) words().give(h->word);
     g_held.fetch_sub((int64_t)bytes);
     delete h;
     return HDA_E_DEVICE;
@@ -348,6 +430,7 @@ int hda_heap_destroy(hda_heap* h) {
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   dev_free(h->dev);
   dev_free(h->io);
+  if (h->word) words().give(h->word);
   g_held.fetch_sub((int64_t)h->bytes);
   delete h;
   return HDA_OK;

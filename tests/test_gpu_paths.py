@@ -87,3 +87,44 @@ def test_ordered_launch_alone(algo):
         db = hda.upload(b, tuning=hda.tuning(heavy_heaps=b.heaps, heavy_kib=kib))
         hda.hda_replay(db)
         check(b, db)
+
+
+@pytest.mark.parametrize("threads", (1, 6))
+def test_heap_calls_from_threads(threads):
+    """Call-by-call heaps side by side (more than a page of result words), each
+    driven by one of several threads, results and states as the oracle's;
+    results of every kind: offsets, -1, refusals, dumps between calls."""
+    import threading
+    A, g, n = 1 << 20, 64, 40
+    heaps = [(hda.Heap(A, g, k % 5), oracle.Heap(k % 5, A, g)) for k in range(70)]
+    say(f"case: {len(heaps)} heaps, {threads} threads, {n} rounds")
+    errors = []
+
+    def drive(t):
+        try:
+            for k in range(t, len(heaps), threads):
+                h, o = heaps[k]
+                rng = np.random.default_rng(k)
+                live = []
+                for i in range(n):
+                    size = int(rng.integers(0, A // 8)) if i % 9 else 2 * A
+                    off = h.alloc(size)
+                    assert off == o.alloc(size)
+                    if off >= 0:
+                        live.append(off)
+                    if live and i % 3 == 0:
+                        x = live.pop(int(rng.integers(len(live))))
+                        assert h.free(x) == o.free(x) == 0
+                        assert h.free(x) == hda.HDA_E_BADFREE
+                assert np.array_equal(h.state(), o.state())
+        except BaseException as e:  # noqa: BLE001
+            errors.append(e)
+
+    ts = [threading.Thread(target=drive, args=(t,)) for t in range(threads)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not errors, errors[0]
+    for h, _ in heaps:
+        h.close()
