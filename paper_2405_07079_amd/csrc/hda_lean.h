@@ -76,20 +76,6 @@ __device__ __forceinline__ void stores_done() {
 #endif
 }
 
-// Lane l of chunk r (both wave-uniform): every chunk's lane l is read and
-// the right one chosen on the scalar unit, which keeps the read free of
-// branches.
-template <int R>
-__device__ __forceinline__ uint32_t reg_lane(const uint32_t (&v)[R], uint32_t r, uint32_t l) {
-  uint32_t x = rdlane(v[0], l);
-#pragma unroll
-  for (int k = 1; k < R; ++k) {
-    const uint32_t y = rdlane(v[k], l);
-    x = (r == (uint32_t)k) ? y : x;
-  }
-  return x;
-}
-
 // The wave's LDS pool: `bytes` (a multiple of 16) from `base`.
 struct LeanLds {
   HDA_LDS uint8_t* base;
@@ -213,12 +199,18 @@ struct LeanHeap {
   }
 
   // ---- free-table entries by wave-uniform index ----
+  // A register chunk is chosen by a branch, like write()'s: one read per
+  // field instead of one per chunk and a select.
+  template <int K = 0>
   __device__ __forceinline__ void read(uint32_t j, uint32_t& a, uint32_t& e, uint32_t& k) {
-    if (j < HF) {
-      const uint32_t r = j >> 6, l = j & 63u;
-      a = reg_lane(fa, r, l);
-      e = reg_lane(fe, r, l);
-      k = kSeg ? reg_lane(fk, r, l) : 0u;
+    if constexpr (K < RF) {
+      if (j < 64u * (K + 1)) {
+        a = rdlane(fa[K], j & 63u);
+        e = rdlane(fe[K], j & 63u);
+        k = kSeg ? rdlane(fk[K], j & 63u) : 0u;
+      } else {
+        read<K + 1>(j, a, e, k);
+      }
     } else {
       wave_sync();
       uint32_t ea, ee, ek;
@@ -230,17 +222,8 @@ struct LeanHeap {
   }
   // The block (address, end) of free entry j.
   __device__ __forceinline__ void read_block(uint32_t j, uint32_t& a, uint32_t& e) {
-    if (j < HF) {
-      const uint32_t r = j >> 6, l = j & 63u;
-      a = reg_lane(fa, r, l);
-      e = reg_lane(fe, r, l);
-    } else {
-      wave_sync();
-      uint32_t ea, ee, ek;
-      cold_get(j, ea, ee, ek);
-      a = uniform(ea);
-      e = uniform(ee);
-    }
+    uint32_t k;
+    read(j, a, e, k);
   }
   __device__ __forceinline__ uint32_t addr_at(uint32_t j) {
     uint32_t a, e;
@@ -273,8 +256,6 @@ struct LeanHeap {
       cold_put<FIELDS>(j, a, e, k);
     }
   }
-  __device__ __forceinline__ void clear(uint32_t j) { write<kBoth>(j, kNone, kNone, kNone); }
-
   // ---- live table ----
   __device__ __forceinline__ void live_write(uint32_t i, uint32_t a, uint32_t s) {
     wave_sync();
@@ -327,30 +308,63 @@ struct LeanHeap {
     write<kBoth>(0, 0u, ag, kSeg ? seg_key(ag) : 0u);
   }
 
-  // Remove free entry j: the last entry moves into its place and the last
-  // slot is cleared.
+  // Read entry j and clear its slot.
+  template <int K = 0>
+  __device__ __forceinline__ void take_out(uint32_t j, uint32_t& a, uint32_t& e, uint32_t& k) {
+    if constexpr (K < RF) {
+      if (j < 64u * (K + 1)) {
+        a = rdlane(fa[K], j & 63u);
+        e = rdlane(fe[K], j & 63u);
+        fa[K] = put_lane(fa[K], j, kNone);
+        fe[K] = put_lane(fe[K], j, kNone);
+        if constexpr (kSeg) {
+          k = rdlane(fk[K], j & 63u);
+          fk[K] = put_lane(fk[K], j, kNone);
+        }
+      } else {
+        take_out<K + 1>(j, a, e, k);
+      }
+    } else {
+      read<RF>(j, a, e, k);
+      wave_sync();
+      cold_put<kBoth>(j, kNone, kNone, kNone);
+    }
+  }
+  // Remove free entry j: the last entry is taken out of its slot and moves
+  // into j's place.
   template <bool CHK = true>
   __device__ __forceinline__ void remove(uint32_t j) {
-    // no branch on j == last: moving the last entry onto itself is harmless
     const uint32_t last = F - 1u;
-    uint32_t a, e, k;
-    read(last, a, e, k);
-    write<kBoth>(j, a, e, k);
-    clear(last);
+    uint32_t a, e, k = 0;
+    take_out(last, a, e, k);
+    if (j != last) write<kBoth>(j, a, e, k);
     F = last;
     if (CHK) set_room();
   }
 
   // Append a free entry (the caller has checked the pool and the capacity).
-  template <bool CHK = true>
+  template <bool CHK = true, int K = 0>
   __device__ __forceinline__ void append(uint32_t a, uint32_t e, uint32_t k) {
-    if (F >= HF && ((F - HF) & 63u) == 0u) {  // a new LDS chunk: its slots start empty
+    if constexpr (K < RF) {
+      if (F < 64u * (K + 1)) {
+        fa[K] = put_lane(fa[K], F, a);
+        fe[K] = put_lane(fe[K], F, e);
+        if constexpr (kSeg) fk[K] = put_lane(fk[K], F, k);
+        ++F;
+        if (CHK) set_room();
+      } else {
+        append<CHK, K + 1>(a, e, k);
+      }
+    } else {
+      if ((F & 63u) == 0u) {  // a new LDS chunk: its slots start empty
+        wave_sync();
+        cold_put<kBoth>(F + lane_id(), kNone, kNone, kNone);
+      }
       wave_sync();
-      cold_put<kBoth>(F + lane_id(), kNone, kNone, kNone);
+      cold_put<kBoth>(F, a, e, k);
+      ++F;
+      if (CHK) set_room();
     }
-    write<kBoth>(F, a, e, k);
-    ++F;
-    if (CHK) set_room();
   }
 
   // Bitmask allocator (Sec. III-B, one flag per granule, searched from the
