@@ -762,10 +762,11 @@ struct OrdHeap {
   // First and next fit: the block at position p of chunk ci (row r current,
   // key e = its last granule, value s = its size) gives sg granules from its
   // low end.
+  template <bool CHK>
   __device__ __forceinline__ int64_t commit_fit(uint32_t ci, uint32_t p, const Row& r,
                                                 uint32_t e, uint32_t s, uint32_t sg) {
     const uint32_t a = e - s + 1u;
-    live_push(a, sg);
+    live_push<CHK>(a, sg);
     if (likely(s > sg)) {
       ta.store_field(ta.slot(ci), p, 1u, s - sg);  // the end stays
       if (kMax) ta.shrink(ci, s, TA::with(r, p, e, s - sg));
@@ -967,12 +968,12 @@ struct OrdHeap {
     if (CHK && full_dir()) return kOverflow;
     if constexpr (ALGO == kFirstFit) {
       const uint32_t ci = ta.first_fit_chunk(sg, 0u);
-      if (ci == kNone) return fail();
+      if (ci == kNone) return fail<CHK>();
       const Row r = ta.load(ta.slot(ci));
       const uint32_t p = ctz64(ballot(r.s >= sg));
       const uint32_t e = rdlane(r.a, p), s = rdlane(r.s, p);
       if (CHK && L >= capL) return kENoMeta;
-      return commit_fit(ci, p, r, e, s, sg);
+      return commit_fit<CHK>(ci, p, r, e, s, sg);
     } else if constexpr (ALGO == kNextFit) {
       // the search starts at the first block ending past the rover (R9-R11)
       // and runs on cyclically: the rest of that chunk, the later chunks,
@@ -987,21 +988,21 @@ struct OrdHeap {
       } else {
         const uint32_t c1 = ta.first_fit_chunk(sg, ci + 1u);
         const uint32_t c2 = c1 != kNone ? c1 : ta.first_fit_chunk(sg, 0u);
-        if (c2 == kNone) return fail();
+        if (c2 == kNone) return fail<CHK>();
         if (c2 != ci) r = ta.load(ta.slot(c2));
         ci = c2;
         p = ctz64(ballot(r.s >= sg));
       }
       const uint32_t e = rdlane(r.a, p), s = rdlane(r.s, p);
       if (CHK && L >= capL) return kENoMeta;
-      return commit_fit(ci, p, r, e, s, sg);
+      return commit_fit<CHK>(ci, p, r, e, s, sg);
     } else if constexpr (ALGO == kBestFit) {
       // smallest key (size, last granule) at or above (sg, 0)
       uint32_t ci, p;
       typename TB::Row r;
       tb.locate(sg, 0u, ci, r, p);
       if (unlikely(p >= tb.count(ci))) {
-        if (ci + 1u >= tb.nc) return fail();
+        if (ci + 1u >= tb.nc) return fail<CHK>();
         ci = ci + 1u;
         r = tb.load(tb.slot(ci));
         p = 0u;
@@ -1015,7 +1016,7 @@ struct OrdHeap {
       ta.locate(0u, e + 1u, cj, ra, q);
       tb.erase_at(ci, p, r);
       if (likely(s > sg)) tb.insert_key(e, s - sg);
-      return commit_fit(cj, q - 1u, ra, e, s, sg);
+      return commit_fit<CHK>(cj, q - 1u, ra, e, s, sg);
     } else {
       // class of the first non-empty list at or above the request's
       uint32_t c;
@@ -1026,20 +1027,20 @@ struct OrdHeap {
           c = (fl << 5) | (uint32_t)__builtin_ctz(m2);
         } else {
           const uint64_t m1 = fl < 63u ? bm & (~0ull << (fl + 1u)) : 0ull;
-          if (m1 == 0ull) return fail();
+          if (m1 == 0ull) return fail<CHK>();
           const uint32_t f2 = ctz64(m1);
           c = (f2 << 5) | (uint32_t)__builtin_ctz(rdlane(slb, f2));
         }
       } else {
         // (a request no larger than the arena has a class below 64)
         const uint64_t mk = bm & (~0ull << kreq);
-        if (mk == 0ull) return fail();
+        if (mk == 0ull) return fail<CHK>();
         c = ctz64(mk);
       }
       const uint32_t i = head(c);
       const Rec b = rec(i);
       if (CHK && L >= capL) return kENoMeta;
-      live_push(b.a, sg);
+      live_push<CHK>(b.a, sg);
       // pop the head (Alg. 4), keeping the lists' invariants (R20)
       set_head(c, b.nx);
       if (b.nx == kNone) bit_clear(c); else rec_link(b.nx, 3u, kNone);
@@ -1225,14 +1226,16 @@ struct OrdHeap {
       nw = lraw(L != 0u ? L - 1u : 0u);
     }
   }
+  template <bool CHK>
   __device__ __forceinline__ int64_t fail() {  // nothing fits
-    look_ahead();
+    if (!CHK) look_ahead();
     return kFail;
   }
+  template <bool CHK>
   __device__ __forceinline__ void live_push(uint32_t a, uint32_t sg) {
     lset(L, mk_ent(a, sg));
     ++L;
-    look_ahead();
+    if (!CHK) look_ahead();
   }
 
   // Whether the next n requests can skip the directory and capacity checks:
