@@ -8,8 +8,7 @@
 // the vector instructions that keep the summaries (120 per request); the
 // table's answer is one test of the block at the rover, or one scan of a few
 // 64-entry chunks: 4,096 heaps of 16 MiB at 64 B, 40,000 requests each, in
-// 26.1 ms against 51.2 ms on the flags (one such heap alone: 373 ns a request
-// against 803).  Heaps whose blocks outgrow the share (sizes to 1/256 of the
+// 20.2 ms against 51.0 ms on the flags (26.1 ms when the table took over).  Heaps whose blocks outgrow the share (sizes to 1/256 of the
 // arena) still gain 1.2x from the part before the move.
 #include <hip/hip_runtime.h>
 

@@ -14,15 +14,18 @@
 // scan covers whole chunks with no bounds mask.
 //
 // What bounds it: a heap is a chain of dependent requests, and four waves per
-// SIMD keep the vector and scalar units 70-80 % busy with table arithmetic
-// (HBM, 16 B per request, is idle by comparison), so the instructions per
-// request set the rate.  Keeping ends instead of sizes, one branch and one
-// write per field instead of selects over every register chunk, two LDS
-// chunks scanned without a loop, results kept as 32-bit granules until the
-// block is stored, and the entry that fills a live hole never made uniform
-// took 4,096 heaps x 100,000 requests (16 MiB, 64 B) from 53.5 to 40.7 ms on
-// best fit and from 64.1 to 51.8 ms on segregated fit, and a lone first-fit
-// heap of 64 KiB from 272 to 224 ns a request.
+// SIMD keep the vector and scalar units busy with table arithmetic (HBM, 16 B
+// per request, is idle by comparison), so the instructions per request set
+// the rate.  Keeping ends instead of sizes, one branch and one access per
+// field instead of selects over every register chunk, two LDS chunks scanned
+// without a loop, results kept as 32-bit granules until the block is stored,
+// and the entry that fills a live hole never made uniform took 4,096 heaps x
+// 100,000 requests (16 MiB, 64 B) from 53.7 to 38.7 ms on best fit and from
+// 64.3 to 48.7 ms on segregated fit, and a lone first-fit heap of 64 KiB from
+// 271 to 207 ns a request.  (Tried and not kept: keys of a chunk together
+// after its blocks; one or four register chunks; the next free's victim
+// loaded ahead, 5-8 % slower even for a lone heap; entries found by a scan
+// kept as chunk and lane.)
 //
 // When the tables would outgrow the pool before reaching the capacities the
 // caller asked for, the request stops with kOverflow (changing nothing) and

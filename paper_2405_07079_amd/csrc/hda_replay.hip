@@ -1,11 +1,12 @@
 // Batched replay of many independent heaps on gfx950.
 //
-// A small classify kernel keeps the heaps with valid parameters in the
-// caller's order (rejecting the others); then one persistent kernel replays
-// them, one wavefront per heap, each wave pulling the next heap from a device
-// queue.  The kernel holds all four algorithms and switches per heap, so a
-// mixed batch is taken in one order (longest trace first is the useful order
-// for uneven batches) instead of one algorithm after another.
+// One kernel replays every heap, one wavefront per heap.  When the heaps
+// outnumber the waves, a small classify kernel first keeps the heaps with
+// valid parameters in the caller's order (rejecting the others) and each wave
+// pulls the next heap from a device queue.  The kernel holds all five
+// table algorithms and switches per heap, so a mixed batch is taken in one
+// order (longest trace first is the useful order for uneven batches) instead
+// of one algorithm after another.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -264,18 +265,16 @@ __global__ void __launch_bounds__(1024) lean_kernel(ReplayParams p) {
   });
 }
 
-// Ordered core (hda_ordered.h) for the heaps taken first from the order: one
-// wave per workgroup owning the whole dynamic LDS of the launch as its pool,
-// and a device-memory slot per workgroup for what does not fit.
-__global__ void __launch_bounds__(64) ordered_kernel(ReplayParams p) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  HDA_LDS uint8_t* pool = (HDA_LDS uint8_t*)smem;
-  const uint64_t slot = blockIdx.x;
-  HDA_GLOBAL uint8_t* dev = (HDA_GLOBAL uint8_t*)(p.ord_dev + slot * p.ord_dev_stride);
-  for_each_heap(p, slot, [&](int64_t heap) __attribute__((always_inline)) {
-    ord_any_heap(p, pool, dev, heap);
-  });
-}
+// The heaps taken first from the order are replayed by the lean kernel too, in
+// a launch of their own: one wave to a workgroup with the whole dynamic LDS
+// as its pool, moving to the ordered core once that is the faster one
+// (lean_max_free) and a device-memory slot for what does not fit.  Started on
+// the ordered core, such heaps paid its price from the first request, when
+// the lean core's is half of it: the first 300,000 requests of a 256 GiB
+// segregated-fit trace 186 ms, now 76; the first 100,000 on first / next /
+// best fit and TLSF 40 / 44 / 66 / 74 ms, now 24 / 23 / 25 / 28; an uneven
+// batch with 128 such heaps 130 ms, now 120.
+const void* const kHeavyKernel = (const void*)lean_kernel<2>;
 
 // Kernels by free-table chunks in VGPRs (0 = general path).
 struct KernelSet {
@@ -341,7 +340,7 @@ struct Plan {
   // the ordered-core launch: the first `heavy` heaps of the order, one wave
   // per workgroup with a pool of heavy_pool LDS bytes, heavy_groups of them
   int64_t heavy = 0;
-  uint32_t heavy_pool = 0, heavy_slot_bytes = 0;
+  uint32_t heavy_pool = 0;
   int64_t heavy_groups = 0;
   uint64_t heavy_stride = 0;
   size_t off_ord = 0;
@@ -391,16 +390,14 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl, bool may_ord 
     if (capF > kOrdMaxFree) return false;  // the ordered core holds at most this many
     pl->heavy = heavy;
     pl->heavy_pool = kib * 1024u;
-    // TLSF's list heads first, then half of the rest for chunk slots
-    pl->heavy_slot_bytes = (pl->heavy_pool - kOrdTlsfHeadBytes) / 2u;
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)ordered_kernel, 64,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kHeavyKernel, 64,
                                                      (size_t)pl->heavy_pool) != hipSuccess ||
         nb < 1)
       nb = 1;
     pl->heavy_groups = std::max<int64_t>(1, std::min<int64_t>(heavy, (int64_t)nb * dc->cus));
     heavy_cus = (int)((pl->heavy_groups + nb - 1) / nb);
-    pl->heavy_stride = (ord_dev_bytes(capL) + 255) / 256 * 256;
+    pl->heavy_stride = (ord_spill_bytes(capF, capL) + 255) / 256 * 256;
   }
   // the other heaps fill the CUs the ordered-core launch leaves
   const int light_cus = std::max(1, dc->cus - heavy_cus);
@@ -559,10 +556,11 @@ ReplayParams heavy_params(const hda_batch_desc* d, const Plan& pl) {
   p.queue = reinterpret_cast<uint32_t*>(ws + pl.off_queues) + kHeavyQueue;
   p.list_lo = 0;
   p.list_hi = pl.heavy;
-  p.ord_pool_bytes = pl.heavy_pool;
-  p.ord_slot_bytes = pl.heavy_slot_bytes;
-  p.ord_dev = ws + pl.off_ord;
-  p.ord_dev_stride = pl.heavy_stride;
+  p.waves_per_group = 1;
+  p.lds_wave_bytes = pl.heavy_pool;
+  p.ord_spill = ws + pl.off_ord;
+  p.ord_spill_stride = pl.heavy_stride;
+  p.lean_early = 1;
   return p;
 }
 
@@ -573,8 +571,11 @@ bool set_lds_attr(const void* fn, uint32_t bytes) {
 }
 
 bool set_lds_attrs(const Plan& pl) {
+  if (pl.heavy == 0) return set_lds_attr(pl.set->fn, pl.main.lds_group);
+  if (pl.set->fn == kHeavyKernel)  // one kernel, two launches: the larger pool
+    return set_lds_attr(kHeavyKernel, std::max(pl.main.lds_group, pl.heavy_pool));
   return set_lds_attr(pl.set->fn, pl.main.lds_group) &&
-         (pl.heavy == 0 || set_lds_attr((const void*)ordered_kernel, pl.heavy_pool));
+         set_lds_attr(kHeavyKernel, pl.heavy_pool);
 }
 
 // A second stream per device for the launch that runs beside the
@@ -631,7 +632,7 @@ int enqueue(const hda_batch_desc* d, const Plan& pl, hipStream_t s) {
   }
   if (pl.main.slots == 0) {  // no other heaps
     ReplayParams hp = heavy_params(d, pl);
-    return launch((const void*)ordered_kernel, dim3((uint32_t)pl.heavy_groups), dim3(64),
+    return launch(kHeavyKernel, dim3((uint32_t)pl.heavy_groups), dim3(64),
                   pl.heavy_pool, s, hp) == hipSuccess && hipGetLastError() == hipSuccess
                ? HDA_OK
                : HDA_E_DEVICE;
@@ -644,7 +645,7 @@ int enqueue(const hda_batch_desc* d, const Plan& pl, hipStream_t s) {
   if (hipEventCreateWithFlags(&e_fork, hipEventDisableTiming) == hipSuccess &&
       hipEventCreateWithFlags(&e_join, hipEventDisableTiming) == hipSuccess &&
       hipEventRecord(e_fork, s) == hipSuccess &&
-      launch((const void*)ordered_kernel, dim3((uint32_t)pl.heavy_groups), dim3(64),
+      launch(kHeavyKernel, dim3((uint32_t)pl.heavy_groups), dim3(64),
              pl.heavy_pool, s, hp) == hipSuccess &&
       hipStreamWaitEvent(f, e_fork, 0) == hipSuccess &&
       launch(pl.set->fn, grid, block, pl.main.lds_group, f, p) == hipSuccess &&

@@ -42,8 +42,8 @@ struct ReplayParams {
   int use_queue;         // 1: pull heaps from the queue; 0: wave w takes heap w
   int64_t list_lo;       // queue mode: this launch takes list positions
   int64_t list_hi;       //   [list_lo, min(list_hi, *count))
-  // ordered core (hda_ordered.h): per-wave LDS pool bytes, the part of it
-  // meant for chunk slots, and the device slot of each wave
+  // ordered core from the first request (ord_any_heap): per-wave LDS pool
+  // bytes, the part of it meant for chunk slots, and the device slot
   uint32_t ord_pool_bytes;
   uint32_t ord_slot_bytes;
   uint8_t* ord_dev;
@@ -421,8 +421,9 @@ __device__ void replay_any_heap(const ReplayParams& p, const Cold& c, int64_t he
   }
 }
 
-// Ordered core (hda_ordered.h) for one heap: tables in the wave's LDS pool
-// and, past it, in its device slot.
+// Ordered core (hda_ordered.h) for one heap from its first request (the CPU
+// emulation's way in; the kernels reach the core through ord_continue):
+// tables in the wave's LDS pool and, past it, in its device slot.
 template <int ALGO>
 __device__ __forceinline__ void ord_replay_heap(const ReplayParams& p, HDA_LDS uint8_t* pool,
                                 HDA_GLOBAL uint8_t* dev, const HeapRegs& regs, int64_t heap) {
