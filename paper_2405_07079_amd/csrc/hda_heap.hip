@@ -4,7 +4,9 @@
 // of the same core as the batched replay, and stores them back.  The result
 // goes straight to the heap's word in pinned host memory, where the caller
 // looks for it: a copy back and a wait for the stream were more than half of
-// a call (22.8 -> 7.9 us for an allocation or a free on a 4 GiB heap).
+// a call (22.8 -> 8.2 us for an allocation or a free on a 4 GiB heap).  The
+// word is the kernel's last store, released after the heap's state (0.2 us of
+// the 8.2).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,32 +28,8 @@ using namespace hda;
 
 namespace {
 
-enum : int { kOpInit = 0, kOpAlloc = 1, kOpFree = 2, kOpDump = 3, kOpFreePartial = 4 };
-
 // What the host word holds until the call's result arrives (no result is it).
 constexpr int64_t kPending = INT64_MIN;
-
-template <int ALGO>
-__device__ void heap_call_t(HeapHdr* hd, int op, int64_t arg, int64_t* dump, int64_t cap,
-                            int64_t* word) {
-  const Cold c = heap_cold(hd);
-  WaveHeap<ALGO, 0, 0> w(c, load_regs(hd), hd->cf, hd->cl);
-  int64_t r = 0;
-  if (op == kOpInit) {
-    w.init();
-  } else if (op == kOpAlloc) {
-    r = arg < 0 ? kEInval : w.alloc_bytes(arg);
-  } else if (op == kOpFree) {
-    r = w.free_offset(arg);
-  } else if (op == kOpFreePartial) {
-    r = w.free_partial(arg);
-  } else {
-    r = w.dump(dump, cap);
-  }
-  if (lane_id() == 0)
-    __hip_atomic_store(word, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  store_regs(hd, w.h);
-}
 
 __global__ void heap_call(HeapHdr* hd, int op, int64_t arg, int64_t* dump, int64_t cap,
                           int64_t* word) {

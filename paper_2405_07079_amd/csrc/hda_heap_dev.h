@@ -1,6 +1,7 @@
-// Device-memory layout of a heap whose state persists between launches:
-// a header holding the wave-uniform registers and the per-class counts,
-// followed by the free table, its push stamps and the live table.
+// A heap whose state persists between launches.  Its device-memory layout: a
+// header holding the wave-uniform registers and the per-class counts,
+// followed by the free table, its push stamps and the live table.  And one
+// call on such a heap by one wave (the kernel of hda_heap.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -50,6 +51,38 @@ __device__ inline void store_regs(HeapHdr* hd, const HeapRegs& h) {
     hd->F = h.F; hd->L = h.L; hd->rover = h.rover; hd->clock = h.clock;
     hd->status = h.status;
   }
+}
+
+enum : int { kOpInit = 0, kOpAlloc = 1, kOpFree = 2, kOpDump = 3, kOpFreePartial = 4 };
+
+// The caller's host thread returns as soon as it sees `r` in *word, so the
+// heap's tables and registers are stored first and the word is released at
+// system scope after them: a call that has returned has nothing left to do on
+// the device but end its kernel.
+__device__ inline void publish(int64_t* word, int64_t r) {
+  wave_sync();  // (every lane has stored its part)
+  if (lane_id() == 0) __hip_atomic_store(word, r, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+template <int ALGO>
+__device__ void heap_call_t(HeapHdr* hd, int op, int64_t arg, int64_t* dump, int64_t cap,
+                            int64_t* word) {
+  const Cold c = heap_cold(hd);
+  WaveHeap<ALGO, 0, 0> w(c, load_regs(hd), hd->cf, hd->cl);
+  int64_t r = 0;
+  if (op == kOpInit) {
+    w.init();
+  } else if (op == kOpAlloc) {
+    r = arg < 0 ? kEInval : w.alloc_bytes(arg);
+  } else if (op == kOpFree) {
+    r = w.free_offset(arg);
+  } else if (op == kOpFreePartial) {
+    r = w.free_partial(arg);
+  } else {
+    r = w.dump(dump, cap);
+  }
+  store_regs(hd, w.h);
+  publish(word, r);
 }
 
 }  // namespace hda
