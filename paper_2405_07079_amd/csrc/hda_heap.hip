@@ -23,6 +23,7 @@
 #include "hda_core.h"
 #include "hda_heap_dev.h"
 #include "hda_mem.h"
+#include "hda_words.h"
 
 using namespace hda;
 
@@ -59,55 +60,31 @@ Allocator& allocator() {
   return a;
 }
 
-// Result words in pinned host memory, one cache line each, 64 to a page: a
-// page is allocated when no word is free and given back when its last word
-// is, but for one empty page (making one takes 0.1 ms, which each heap would
-// pay).
-class WordPool {
-  struct Page {
-    uint8_t* host;
-    uint64_t used;  // bit i: word i is a heap's
-  };
-  std::mutex mu_;
-  std::vector<Page> pages_;
-
- public:
-  int64_t* take() {
-    std::lock_guard<std::mutex> g(mu_);
-    for (Page& p : pages_)
-      if (~p.used) {
-        const int i = __builtin_ctzll(~p.used);
-        p.used |= 1ull << i;
-        return reinterpret_cast<int64_t*>(p.host + 64 * i);
-      }
-    void* host = nullptr;
-    if (hipHostMalloc(&host, 4096, hipHostMallocCoherent | hipHostMallocMapped |
-                                       hipHostMallocPortable) != hipSuccess)
-      return nullptr;
-    pages_.push_back({static_cast<uint8_t*>(host), 1ull});
-    return static_cast<int64_t*>(host);
-  }
-  void give(int64_t* w) {
-    std::lock_guard<std::mutex> g(mu_);
-    uint8_t* b = reinterpret_cast<uint8_t*>(w);
-    size_t empty = 0, at = pages_.size();
-    for (size_t k = 0; k < pages_.size(); ++k) {
-      Page& p = pages_[k];
-      if (b >= p.host && b < p.host + 4096) {
-        p.used &= ~(1ull << ((b - p.host) / 64));
-        if (p.used == 0) at = k;
-      }
-      empty += p.used == 0;
-    }
-    if (at < pages_.size() && empty > 1) {
-      (void)hipHostFree(pages_[at].host);
-      pages_.erase(pages_.begin() + (std::ptrdiff_t)at);
-    }
-  }
-};
 WordPool& words() {
   static WordPool* w = new WordPool;  // (never destroyed: heaps may outlive statics)
   return *w;
+}
+int64_t* take_word() {
+  return words().take([]() -> void* {
+    void* host = nullptr;
+    return hipHostMalloc(&host, WordPool::kPageBytes,
+                         hipHostMallocCoherent | hipHostMallocMapped | hipHostMallocPortable) ==
+                   hipSuccess
+               ? host
+               : nullptr;
+  });
+}
+// Without an installed allocator the heap's tables have just gone through
+// hipFree, which waits for the device as hipHostFree does, so an empty page is
+// freed too; with one, whose release may not wait, giving up a heap does not.
+void give_word(int64_t* w) {
+  bool drop;
+  {
+    Allocator& a = allocator();
+    std::lock_guard<std::mutex> g(a.mu);
+    drop = a.release == nullptr;
+  }
+  if (void* page = words().give(w, drop)) (void)hipHostFree(page);
 }
 
 }  // namespace
@@ -375,11 +352,11 @@ int hda_heap_create(uint64_t arena_bytes, uint64_t align, int algo, uint32_t met
   h->align = align;
   h->cap = cap;
   h->stream = lib_stream();
-  if (h->stream && (h->word = words().take()) != nullptr &&
+  if (h->stream && (h->word = take_word()) != nullptr &&
       hipHostGetDevicePointer((void**)&h->dev_word, h->word, 0) == hipSuccess)
     h->dev = static_cast<HeapHdr*>(dev_alloc(bytes));
   if (!h->dev) {
-    if (h->word) words().give(h->word);
+    if (h->word) give_word(h->word);
     g_held.fetch_sub((int64_t)bytes);
     delete h;
     return HDA_E_DEVICE;
@@ -408,7 +385,7 @@ int hda_heap_destroy(hda_heap* h) {
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   dev_free(h->dev);
   dev_free(h->io);
-  if (h->word) words().give(h->word);
+  if (h->word) give_word(h->word);
   g_held.fetch_sub((int64_t)h->bytes);
   delete h;
   return HDA_OK;
