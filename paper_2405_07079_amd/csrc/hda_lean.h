@@ -124,7 +124,8 @@ struct LeanHeap {
   // faster; first fit 0.5 % slower, which takes constants).
   static constexpr bool kColdId = ALGO == kBestFit || kSeg;
   uint32_t cold_id[2];
-  uint32_t max_free = kNone;      // hand the heap over past this many free blocks
+  uint32_t leave_past = kNone, leave_most = 0u;  // hand the heap over with more free blocks
+                                                 // than the first, but not the second
   uint32_t capF, capL;            // the caller's capacities (E_NOMETA past them)
   uint32_t live_room;             // live entries the pool holds beside the current free chunks
 

@@ -544,7 +544,7 @@ ReplayParams replay_params(const hda_batch_desc* d, const Plan& pl) {
   p.list_hi = INT64_MAX;
   p.ord_spill = pl.ord_spill ? ws + ps.off_ord : nullptr;
   p.ord_spill_stride = ps.ord_stride;
-  p.lean_early = ps.lds_wave >= kEarlyPool;
+  p.lean_early = ps.lds_wave >= kEarlyPool ? kEarlyMain : kEarlyNever;
   return p;
 }
 
@@ -560,7 +560,7 @@ ReplayParams heavy_params(const hda_batch_desc* d, const Plan& pl) {
   p.lds_wave_bytes = pl.heavy_pool;
   p.ord_spill = ws + pl.off_ord;
   p.ord_spill_stride = pl.heavy_stride;
-  p.lean_early = 1;
+  p.lean_early = kEarlyHeavy;
   return p;
 }
 

@@ -52,8 +52,11 @@ struct ReplayParams {
   // (ord_spill_bytes), or null
   uint8_t* ord_spill;
   uint64_t ord_spill_stride;
-  int lean_early;          // a heap goes there once scans cost more (lean_max_free)
+  int lean_early;          // when it goes there (early_limit)
 };
+// ReplayParams::lean_early: only once the pool is outgrown; also once scans
+// cost more; the same in the launch of the heaps taken first from the order.
+enum : int { kEarlyNever = 0, kEarlyMain = 1, kEarlyHeavy = 2 };
 
 // Validate heap parameters; on success fill the uniform heap registers.
 __device__ __forceinline__ bool heap_params(const ReplayParams& p, int64_t heap, HeapRegs& h) {
@@ -178,7 +181,7 @@ __device__ __forceinline__ int64_t run_requests(const ReplayParams& p, Core& w, 
   int64_t nxt = to > from ? p.req[min<int64_t>(from + lane, last)] : 0;
   for (int64_t base = from; base < to; base += 64) {
     if constexpr (LeavesEarly<Core>::value)
-      if (w.F > w.max_free) return base;
+      if (w.F > w.leave_past && w.F <= w.leave_most) return base;
     const int64_t q = nxt;
     nxt = p.req[min<int64_t>(base + 64 + lane, last)];
     const bool is_free = q < 0;
@@ -323,6 +326,30 @@ __device__ __forceinline__ constexpr uint32_t lean_max_free(int algo) {
   return algo == kFirstFit ? 256u : algo == kNextFit ? 384u : algo == kBestFit ? 1024u : 512u;
 }
 
+// The most free blocks a heap may bring to the ordered core: adopt()'s share
+// of the slot, and one directory register, which describes 64 chunks (adopt()
+// fills 56 entries of each, so 63 full ones leave a chunk to spare).
+__device__ __forceinline__ constexpr uint32_t ord_most_free(uint32_t cap_free) {
+  return ord_adopt_max(cap_free) < 56u * 63u ? ord_adopt_max(cap_free) : 56u * 63u;
+}
+
+// The limit for one launch and capacity.  It is looked at once per block of 64
+// requests, each of which may add a free block, so a heap has up to limit + 64
+// of them by then.  Where the ordered core does not take that many (capacities
+// near the limit) leaving could end on the general core, the slowest.  The
+// main launch hands over only what the ordered core takes (run_requests) and
+// keeps the heap in its pool otherwise.  The heavy launch, whose pools may be
+// small and whose heaps were on the ordered core from the first request before
+// they started on the lean one, hands over while the ordered core still takes
+// the heap.  64 heaps of small blocks in 64 KiB pools, first fit at a capacity
+// of 320 free blocks / next fit at 512 / segregated fit at 640: on the general
+// core 17.0 / 24.1 / 25.9 ms, on the ordered core throughout 8.2 / 9.7 / 11.0,
+// now 6.9 / 7.4 / 10.3.
+__device__ __forceinline__ constexpr uint32_t early_limit(int algo, uint32_t cap_free, int early) {
+  const uint32_t limit = lean_max_free(algo), most = ord_most_free(cap_free);
+  return early != kEarlyHeavy || limit + 64u <= most ? limit : most > 64u ? most - 64u : 0u;
+}
+
 template <int ALGO>
 __device__ __forceinline__ OrdMem ord_spill_mem(const ReplayParams& p, HDA_LDS uint8_t* pool,
                                                 uint32_t pool_bytes, HDA_GLOBAL uint8_t* ord) {
@@ -345,16 +372,17 @@ __device__ __forceinline__ LeanExit lean_start(const ReplayParams& p, const Lean
   LeanHeap<ALGO, RF> w(lds, h, p.cap_free, p.cap_live);
   w.init();
   const int64_t b1 = p.req_off[heap + 1];
-  w.max_free = ord != nullptr && p.lean_early ? lean_max_free(ALGO) : kNone;
+  if (ord != nullptr && p.lean_early != kEarlyNever) {
+    w.leave_past = early_limit(ALGO, p.cap_free, p.lean_early);
+    w.leave_most = ord_most_free(p.cap_free);
+  }
   x.pos = run_requests<ALGO>(p, w, p.req_off[heap], b1, w.shift, w.arena, x.st);
   if (x.pos == b1) {
     finish_heap(p, w, heap, x.st);
     return x;
   }
   if (lane_id() == 0 && p.migrated) atomicAdd(p.migrated, 1u);
-  // (one directory register describes 64 chunks; adopt() fills 56 entries of
-  // each, so that many free blocks leave a chunk to spare)
-  if (ord != nullptr && w.F <= ord_adopt_max(p.cap_free) && w.F <= 56u * 63u) {
+  if (ord != nullptr && w.F <= ord_most_free(p.cap_free)) {
     x.next = LeanExit::kOrdered;
     OrdHeap<ALGO, 1>(ord_spill_mem<ALGO>(p, lds.base, lds.bytes, ord), h, p.cap_free,
                      p.cap_live).stage(w);
