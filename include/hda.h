@@ -125,8 +125,9 @@ int hda_set_device_allocator(hda_dev_alloc_fn alloc, hda_dev_free_fn release, vo
  * 64*reg_free free-table entries are held in vector registers (reg_free = 1,
  * 2 or 4; 0 = 2); the rest of the free table and the whole live table share
  * one LDS pool per heap of lds_free * 16 + lds_live * 8 bytes (defaults 128
- * and 1024: 10 KiB; 2, 4 or 6 times that when so few heaps are in the batch
- * that a CU holds 8, 4 or 2 of them), free entries from its start and live entries from its
+ * and 1024: 10 KiB; 2, 4 or 6 times that for batches of so few heaps that
+ * four of them fit the device's LDS side by side, on streams of their own),
+ * free entries from its start and live entries from its
  * end.  A heap whose tables outgrow the pool before reaching meta_free /
  * meta_live moves them, mid-trace, to the ordered core (pools of 10 KiB or
  * more, meta_free up to 4,096, and a workspace that holds its slots; else to

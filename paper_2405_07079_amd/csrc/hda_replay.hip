@@ -287,6 +287,7 @@ const KernelSet kSets[] = {{0, (const void*)general_kernel},
                            {4, (const void*)lean_kernel<4>}};
 constexpr int kDefaultRF = 2;
 constexpr uint32_t kEarlyPool = 20480;  // pools that leave at most two waves a SIMD
+constexpr int64_t kQueues = 4;  // launches a device runs side by side (hardware queues a process has)
 
 const KernelSet* find_set(int rf) {
   for (const KernelSet& s : kSets)
@@ -401,12 +402,17 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl, bool may_ord 
   }
   // the other heaps fill the CUs the ordered-core launch leaves
   const int light_cus = std::max(1, dc->cus - heavy_cus);
-  // Lean launches by the waves per CU (of the 16 its registers allow) that
-  // put every heap in flight: few heaps run one or two to a workgroup, spread
-  // over the CUs, and get the LDS the others would have had -- 60, 40 or 20
-  // KiB, within the 64 KiB a workgroup has without asking (2,000 mixed heaps
-  // of small blocks 14.2 -> 11.7 ms, one best-fit heap 18.1 -> 12.7 ms,
-  // against pools of 10 KiB that they outgrow).
+  // Lean launches of few heaps run one or two to a workgroup, spread over the
+  // CUs, and get a larger pool each: 60, 40 or 20 KiB, within the 64 KiB a
+  // workgroup has without asking (500 first-fit heaps of small blocks 9.4 ->
+  // 7.0 ms, one best-fit heap 18.1 -> 12.3 ms, against pools of 10 KiB that
+  // they outgrow).  Only as large as lets kQueues such batches on streams of
+  // their own fit the LDS together: a device runs that many at a time, and
+  // pools sized for one batch alone made the others wait (four streams of
+  // 1,000 best-fit heaps, 4,000 requests each: 4.17 ms with 40 KiB, 1.37 ms
+  // with 10; of 512: 4.00 ms with 60, 1.35 with 20; of 256: 2.08 with 60, 1.30
+  // with 40.  Alone, 1,000 next-fit heaps of small blocks pay 5.5 ms for 4.9,
+  // 2,000 mixed ones 13.5 for 11.6).
   const int64_t light = std::max<int64_t>(d->n_heaps - heavy, 1);
   const int64_t per_cu = (light + light_cus - 1) / light_cus;
   const bool sized = lean && persistent && tu.groups == 0;
@@ -432,11 +438,14 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl, bool may_ord 
     m.lds_free = want_kf;
     m.lds_live = want_kl;
     if (sized && tu.lds_free == 0 && tu.lds_live == 0) {
-      const uint32_t more = per_cu <= 2 ? 6u : per_cu <= 4 ? 4u : per_cu <= 8 ? 2u : 1u;
-      if (W * more * (want_kf * 16u + want_kl * 8u) <= 65536u) {
-        m.lds_free *= more;
-        m.lds_live *= more;
-      }
+      const int64_t waves = (kQueues * light + light_cus - 1) / light_cus;
+      const uint32_t pool = want_kf * 16u + want_kl * 8u;
+      const auto fits = [&](uint32_t more) {
+        return (size_t)waves * more * pool <= dc->max_lds && W * more * pool <= 65536u;
+      };
+      const uint32_t more = fits(6u) ? 6u : fits(4u) ? 4u : fits(2u) ? 2u : 1u;
+      m.lds_free *= more;
+      m.lds_live *= more;
     }
     m.lds_wave = (m.lds_free * 16u + m.lds_live * 8u + 15u) & ~15u;
   } else {
