@@ -84,6 +84,9 @@ __device__ __forceinline__ uint32_t longest_run(uint64_t w) {
 }
 
 constexpr uint32_t kNodeGranules = 4096;  // 64 words
+// A node with every granule free; a mark that is no summary.
+constexpr uint64_t kNodeFree = 0x0000100010001000ull;
+constexpr uint64_t kNodeUnknown = ~0ull;
 
 // Node summary word: bottom run | top run << 16 | longest run << 32 (each
 // 0..4096 granules; the longest run may be an upper bound).  0 = no free
@@ -228,6 +231,13 @@ struct BitHeap {
   // memory, the flags are set block by block (word wi is always written by
   // lane wi % 64), then summaries and the first live entries go to LDS, which
   // holds nothing else by then.
+  //
+  // Only the nodes a block begins or ends in are read (their flags hold other
+  // blocks too, and their summaries are taken from the flags at the end): the
+  // nodes inside a block and those without a free granule are stored, so a
+  // large arena costs stores, not a wait for each node (20,000 requests on
+  // 2^28 granules 132 -> 80 ms, on 2^31 955 -> 555; with flags from the
+  // first request 81 / 549).
   template <typename Lean>
   __device__ void take(Lean& t) {
     const uint32_t lane = lane_id();
@@ -239,18 +249,36 @@ struct BitHeap {
     }
     for (uint32_t w0 = 0; w0 < nw; w0 += 64u)
       if (w0 + lane < nw) bits[w0 + lane] = 0ull;
+    for (uint32_t n0 = 0; n0 < nn; n0 += 64u)
+      if (n0 + lane < nn && n0 + lane >= kn) nodes[n0 + lane] = 0ull;
+    stores_done();
     for (uint32_t j = 0; j < t.F; ++j) {
       uint32_t a, e, k;
       t.read(j, a, e, k);
-      const uint32_t s = e - a, last = (e - 1u) >> 6;
-      for (uint32_t n = a >> 12; n <= (last >> 6); ++n) {
+      const uint32_t first = a >> 12, last = (e - 1u) >> 12;  // nodes
+      for (uint32_t n = first; n <= last; ++n) {
         const uint32_t wi = 64u * n + lane;
-        const uint64_t m = word_mask(wi, a, s);
-        const uint64_t v = load(wi) | m;
-        if (m != 0ull) bits[wi] = v;
+        uint64_t m = ~0ull;
+        if (n == first || n == last) {
+          m = word_mask(wi, a, e - a);
+          m = m != 0ull ? load(wi) | m : 0ull;
+        }
+        if (m != 0ull) bits[wi] = m;
+      }
+      for (uint32_t n0 = first; n0 <= last; n0 += 64u) {
+        const uint32_t n = n0 + lane;
+        if (n <= last && n >= kn) nodes[n] = n == first || n == last ? kNodeUnknown : kNodeFree;
       }
     }
-    for (uint32_t n = 0; n < nn; ++n) put_node(n, node_summary(load(64u * n + lane)));
+    stores_done();
+    for (uint32_t n0 = 0; n0 < nn; n0 += 64u) {
+      const uint32_t n = n0 + lane;
+      const uint64_t v = nodes[n < nn ? n : nn - 1u];
+      for (uint64_t m = ballot(n < nn && (n < kn || v == kNodeUnknown)); m != 0ull; m &= m - 1ull) {
+        const uint32_t u = n0 + ctz64u(m);
+        put_node(u, node_summary(load(64u * u + lane)));
+      }
+    }
     for (uint32_t base = 0; base < t.L && base < kl; base += 64u) {
       const uint32_t i = base + lane;
       wave_sync();

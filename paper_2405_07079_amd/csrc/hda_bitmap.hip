@@ -51,32 +51,64 @@ __global__ void bitmap_reset(uint32_t* queue) {
   if (threadIdx.x == 0) *queue = 0u;
 }
 
-__global__ __launch_bounds__(64 * kWavesPerGroup) void bitmap_kernel(ReplayParams p,
-                                                                     uint64_t* ws,
-                                                                     uint64_t max_granules,
-                                                                     uint64_t words,
-                                                                     int64_t waves) {
+struct BitmapParams {
+  ReplayParams p;
+  uint64_t* ws;
+  uint64_t max_granules;
+  uint64_t words;  // of a wave's slot
+  int64_t waves;
+};
+typedef const __attribute__((address_space(4))) BitmapParams* LaunchParams;
+
+// The two parts of a heap's replay as functions of their own, each compiled by
+// itself: in one function the flags part, which most heaps never reach, took
+// registers from the table's request loop (2 % on 4,096 heaps).  At most two
+// calls a heap.  Arguments are wave-uniform but for BitmapExit's chunks; the
+// kernel's parameters are read from where the launch put them.
+struct WaveEnv {
+  BitmapParams b;
+  LeanLds lds;
+  __device__ __forceinline__ WaveEnv(LaunchParams lp, uint32_t pool) {
+    __builtin_memcpy(&b, (const void*)(LaunchParams)uniform64((uint64_t)lp), sizeof(b));
+    lds.base = (HDA_LDS uint8_t*)(uintptr_t)uniform(pool);
+    lds.bytes = kLdsWaveBytes;
+  }
+};
+__device__ __attribute__((noinline)) BitmapExit table_call(LaunchParams lp, uint32_t pool,
+                                                           uint32_t heap) {
+  const WaveEnv e(lp, pool);
+  return bitmap_start(e.b.p, e.lds, e.b.max_granules, (int64_t)uniform(heap));
+}
+__device__ __attribute__((noinline)) void flags_call(LaunchParams lp, uint32_t pool,
+                                                     uint32_t wave, uint32_t heap, BitmapExit x) {
+  const WaveEnv e(lp, pool);
+  uint64_t* bits = e.b.ws + kHeaderBytes / 8u + (uint64_t)uniform(wave) * e.b.words;
+  uint64_t* nodes = bits + flag_words(e.b.max_granules);
+  Ent* live = reinterpret_cast<Ent*>(nodes + node_words(e.b.max_granules));
+  x.st = (int32_t)uniform((uint32_t)x.st);
+  x.pos = (int64_t)uniform64((uint64_t)x.pos);
+  x.F = uniform(x.F); x.L = uniform(x.L); x.rover = uniform(x.rover);
+  bitmap_continue(e.b.p, e.lds, bits, nodes, live, kLdsNodes, (int64_t)uniform(heap), x);
+}
+
+__global__ __launch_bounds__(64 * kWavesPerGroup) void bitmap_kernel(BitmapParams b) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const uint32_t wl = uniform(threadIdx.x / 64u);
-  const int64_t wave = uniform(blockIdx.x * kWavesPerGroup + wl);
-  if (wave >= waves) return;
-  uint32_t* queue = reinterpret_cast<uint32_t*>(ws);
-  uint64_t* slot = ws + kHeaderBytes / 8u + (uint64_t)wave * words;
-  uint64_t* bits = slot;
-  uint64_t* nodes = slot + flag_words(max_granules);
-  Ent* live = reinterpret_cast<Ent*>(nodes + node_words(max_granules));
-  LeanLds lds;
-  lds.base = (HDA_LDS uint8_t*)smem + (size_t)wl * kLdsWaveBytes;
-  lds.bytes = kLdsWaveBytes;
+  const uint32_t wave = uniform(blockIdx.x * kWavesPerGroup + wl);
+  if ((int64_t)wave >= b.waves) return;
+  const uint32_t pool = (uint32_t)(uintptr_t)((HDA_LDS uint8_t*)smem) + wl * kLdsWaveBytes;
+  const LaunchParams lp = (LaunchParams)__builtin_amdgcn_kernarg_segment_ptr();
+  uint32_t* queue = reinterpret_cast<uint32_t*>(b.ws);
   // a wave takes at most every heap, so the loop ends even if the queue were
   // never to run dry; every lane runs the atomic (lane 0 adds 1) so the value
   // read back does not come from a lane-dependent branch
-  for (int64_t taken = 0; taken < p.n_heaps; ++taken) {
+  for (int64_t taken = 0; taken < b.p.n_heaps; ++taken) {
     uint32_t i = atomicAdd(queue, lane_id() == 0 ? 1u : 0u);
     i = rdlane(i, 0);
-    if ((int64_t)i >= p.n_heaps) break;
-    bitmap_lean_heap(p, lds, bits, nodes, live, kLdsNodes, max_granules,
-                     p.order ? p.order[i] : (int64_t)i);
+    if ((int64_t)i >= b.p.n_heaps) break;
+    const uint32_t heap = b.p.order ? (uint32_t)b.p.order[i] : i;
+    const BitmapExit x = table_call(lp, pool, heap);
+    if (uniform((uint32_t)x.next)) flags_call(lp, pool, wave, heap, x);
   }
 }
 
@@ -106,24 +138,27 @@ int hda_bitmap_replay(const hda_batch_desc* d, uint64_t max_granules, void* stre
   if (d->n_heaps == 0) return HDA_OK;
   const size_t need = hda_bitmap_workspace(d, max_granules);
   if (!d->workspace || d->workspace_bytes < need) return HDA_E_RANGE;
-  ReplayParams p;
-  std::memset(&p, 0, sizeof(p));
+  BitmapParams b;
+  std::memset(&b, 0, sizeof(b));
+  ReplayParams& p = b.p;
   p.arena = d->arena; p.align = d->align; p.algo = d->algo;
   p.req_off = d->req_off; p.req = d->req; p.res = d->res; p.order = d->order;
   p.state = d->state; p.state_off = d->state_off; p.state_len = d->state_len;
   p.status = d->status;
   p.n_heaps = d->n_heaps;
   p.cap_live = (uint32_t)d->meta_live;
-  const int64_t waves = n_waves(d->n_heaps);
-  const uint32_t groups = (uint32_t)((waves + kWavesPerGroup - 1) / kWavesPerGroup);
   uintptr_t base = reinterpret_cast<uintptr_t>(d->workspace);
   base = (base + 255u) & ~uintptr_t(255);
+  b.ws = reinterpret_cast<uint64_t*>(base);
+  b.max_granules = max_granules;
+  b.words = slot_words(max_granules, d->meta_live);
+  b.waves = n_waves(d->n_heaps);
+  const uint32_t groups = (uint32_t)((b.waves + kWavesPerGroup - 1) / kWavesPerGroup);
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipLaunchKernelGGL(bitmap_reset, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(base));
   if (hipGetLastError() != hipSuccess) return HDA_E_DEVICE;
   hipLaunchKernelGGL(bitmap_kernel, dim3(groups), dim3(64 * kWavesPerGroup),
-                     kLdsWaveBytes * kWavesPerGroup, s, p, reinterpret_cast<uint64_t*>(base),
-                     max_granules, slot_words(max_granules, d->meta_live), waves);
+                     kLdsWaveBytes * kWavesPerGroup, s, b);
   return hipGetLastError() == hipSuccess ? HDA_OK : HDA_E_DEVICE;
 }
 

@@ -106,6 +106,19 @@ __device__ __forceinline__ Ent mk_ent(uint32_t a, uint32_t s) { return ((uint64_
 __device__ __forceinline__ uint32_t ent_a(Ent e) { return (uint32_t)e; }
 __device__ __forceinline__ uint32_t ent_s(Ent e) { return (uint32_t)(e >> 32); }
 
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
+}
+
+// Stores so far are complete before any later one is issued (words that one
+// lane clears and another then writes).
+__device__ __forceinline__ void stores_done() {
+  wave_sync();
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+}
+
 // Cold storage of a heap's tables: cold entry i of the free (live) table is
 // at LDS index i while i < kf (kl), and at device index i - kf (i - kl) after.
 struct Cold {

@@ -70,15 +70,6 @@ __device__ __forceinline__ uint32_t keep_scalar(uint32_t v) {
   return v;
 }
 
-// Stores so far are complete before any later one is issued (words that one
-// lane clears and another then writes).
-__device__ __forceinline__ void stores_done() {
-  wave_sync();
-#ifdef __HIP_DEVICE_COMPILE__
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#endif
-}
-
 // The wave's LDS pool: `bytes` (a multiple of 16) from `base`.
 struct LeanLds {
   HDA_LDS uint8_t* base;

@@ -181,10 +181,6 @@ __global__ void __launch_bounds__(1024) general_kernel(ReplayParams p) {
 // kernel's parameters are read from where the launch put them.
 typedef const __attribute__((address_space(4))) ReplayParams* LaunchParams;
 
-__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
-  return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
-}
-
 // What a part works with: the launch's parameters, the wave's pool and its
 // device-memory slot for a heap that outgrows the pool -- the ordered core's
 // (which also holds the general core's tiers), or the general core's alone.

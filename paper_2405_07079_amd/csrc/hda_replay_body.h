@@ -482,30 +482,65 @@ __device__ __forceinline__ void ord_any_heap(const ReplayParams& p, HDA_LDS uint
 // wave's LDS pool; a heap whose tables outgrow the pool continues on the
 // flags (hda_bitmap.h) in the wave's workspace slot, the first kn summaries
 // and kl live entries in the same LDS.
+//
+// Where a heap stands when it leaves the table: the first request not run,
+// and the table, whose first chunks (fa, fe: per lane) are in registers and
+// whose rest and live entries are still in the pool.
+struct BitmapExit {
+  int32_t next, st;      // next: 0 the heap is finished, 1 it goes on on the flags
+  int64_t pos;
+  uint32_t F, L, rover;
+  uint32_t fa[kBitmapRF], fe[kBitmapRF];
+};
+
+__device__ __forceinline__ BitmapExit bitmap_start(const ReplayParams& p, const LeanLds& lds,
+                                                   uint64_t max_granules, int64_t heap) {
+  BitmapExit x{};
+  HeapRegs h;
+  if (!heap_params(p, heap, h) || h.algo != kBitmap || (uint64_t)h.ag > max_granules) {
+    reject_heap(p, heap);
+    return x;
+  }
+  LeanHeap<kBitmap, kBitmapRF> w(lds, h, kNone, p.cap_live);
+  w.init();
+  const int64_t b1 = p.req_off[heap + 1];
+  x.pos = run_requests<kBitmap>(p, w, p.req_off[heap], b1, h.shift, h.arena, x.st);
+  if (x.pos == b1) {
+    finish_heap(p, w, heap, x.st);
+    return x;
+  }
+  if (lane_id() == 0 && p.migrated) atomicAdd(p.migrated, 1u);
+  x.next = 1;
+  x.F = w.F; x.L = w.L; x.rover = w.rover;
+#pragma unroll
+  for (int k = 0; k < kBitmapRF; ++k) { x.fa[k] = w.fa[k]; x.fe[k] = w.fe[k]; }
+  return x;
+}
+
+__device__ __forceinline__ void bitmap_continue(const ReplayParams& p, const LeanLds& lds,
+                                                uint64_t* bits, uint64_t* nodes, Ent* live,
+                                                uint32_t kn, int64_t heap, const BitmapExit& x) {
+  HeapRegs h;
+  if (!heap_params(p, heap, h)) return;  // (they were valid when the heap started)
+  LeanHeap<kBitmap, kBitmapRF> w(lds, h, kNone, p.cap_live);
+  w.F = x.F; w.L = x.L; w.rover = x.rover;
+#pragma unroll
+  for (int k = 0; k < kBitmapRF; ++k) { w.fa[k] = x.fa[k]; w.fe[k] = x.fe[k]; }
+  BitHeap b(bits, nodes, live, (HDA_LDS uint64_t*)lds.base, kn,
+            (HDA_LDS Ent*)(lds.base + 8u * kn), (lds.bytes - 8u * kn) / 8u, h, p.cap_live);
+  b.take(w);
+  int32_t st = x.st;
+  run_requests<kBitmap>(p, b, x.pos, p.req_off[heap + 1], h.shift, h.arena, st);
+  finish_heap(p, b, heap, st);
+}
+
+// Both parts in place (the GPU kernel calls them out of line, hda_bitmap.hip).
 __device__ __forceinline__ void bitmap_lean_heap(const ReplayParams& p, const LeanLds& lds,
                                                  uint64_t* bits, uint64_t* nodes, Ent* live,
                                                  uint32_t kn, uint64_t max_granules,
                                                  int64_t heap) {
-  HeapRegs h;
-  if (!heap_params(p, heap, h) || h.algo != kBitmap || (uint64_t)h.ag > max_granules) {
-    reject_heap(p, heap);
-    return;
-  }
-  LeanHeap<kBitmap, kBitmapRF> w(lds, h, kNone, p.cap_live);
-  w.init();
-  int32_t st = 0;
-  const int64_t b1 = p.req_off[heap + 1];
-  const int64_t pos = run_requests<kBitmap>(p, w, p.req_off[heap], b1, h.shift, h.arena, st);
-  if (pos == b1) {
-    finish_heap(p, w, heap, st);
-    return;
-  }
-  BitHeap b(bits, nodes, live, (HDA_LDS uint64_t*)lds.base, kn,
-            (HDA_LDS Ent*)(lds.base + 8u * kn), (lds.bytes - 8u * kn) / 8u, h, p.cap_live);
-  b.take(w);
-  if (lane_id() == 0 && p.migrated) atomicAdd(p.migrated, 1u);
-  run_requests<kBitmap>(p, b, pos, b1, h.shift, h.arena, st);
-  finish_heap(p, b, heap, st);
+  const BitmapExit x = bitmap_start(p, lds, max_granules, heap);
+  if (x.next) bitmap_continue(p, lds, bits, nodes, live, kn, heap, x);
 }
 
 // Bitmask-allocator replay of one heap (hda_bitmap.h) in a workspace slot
