@@ -456,7 +456,11 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl, bool may_ord 
     m.lds_live = m.kl;
   }
   m.lds_group = m.lds_wave * W;
-  if (m.lds_group > dc->max_lds) return false;
+  // whether LDS sizes asked for are too large does not depend on how many
+  // heaps there are: without heaps_per_group they are looked at for 4 waves
+  const bool asked = tu.lds_free != 0 || tu.lds_live != 0;
+  const uint32_t most_waves = persistent && tu.heaps_per_group == 0 && asked ? 4u : W;
+  if ((size_t)m.lds_wave * most_waves > dc->max_lds) return false;
   pl->ord_spill = lean && may_ord && capF <= kOrdMaxFree && m.lds_wave >= kOrdMinPool;
   if (pl->ord_spill) m.sf = m.sl = 0;
   m.groups = persistent ? occupancy_groups(set->fn, W, m.lds_group, light_cus, tu.groups,
