@@ -8,7 +8,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libhda.so")
 SOURCES = ["hda_replay.hip", "hda_heap.hip", "hda_serve.hip", "hda_bitmap.hip"]
 HEADERS = ["hda_wave.h", "hda_core.h", "hda_lean.h", "hda_ordered.h", "hda_bitmap.h", "hda_replay_body.h",
-           "hda_heap_dev.h", "hda_mem.h", "hda_words.h"]
+           "hda_heap_dev.h", "hda_mem.h", "hda_tune.h", "hda_words.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",

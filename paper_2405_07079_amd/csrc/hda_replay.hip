@@ -22,6 +22,7 @@
 #include "hda_replay_body.h"
 #include "hda_ordered.h"
 #include "hda_mem.h"
+#include "hda_tune.h"
 
 using namespace hda;
 
@@ -927,21 +928,12 @@ int hda_replay_autotune(const hda_batch_desc* d, int32_t sample_heaps, void* str
   // each trace cut to its first kCut requests
   const int64_t want = sample_heaps > 0 ? sample_heaps : pl.main.slots;
   const std::vector<int32_t> sample = longest_heaps(off, want, dc->cus, kBudget, kCut);
-  std::vector<hda_tuning> cand;
-  const uint32_t lds_pairs[][2] = {{64, 512}, {128, 1024}, {256, 2048}, {512, 4096}};
-  for (int32_t W : {1, 2, 4, 8, 16})
-    for (const auto& kv : lds_pairs) {
-      hda_tuning t = d->tuning;
-      t.heaps_per_group = W;
-      t.reg_free = t.reg_free < 0 ? 0 : t.reg_free;
-      t.reg_live = 0;
-      t.lds_free = (int32_t)kv[0];
-      t.lds_live = (int32_t)kv[1];
-      t.groups = 0;
-      t.heavy_heaps = 0;
-      t.heavy_kib = 0;
-      cand.push_back(t);
-    }
+  hda_batch_desc dz = *d;  // the default plan, on the lean path
+  dz.tuning = hda_tuning{};
+  dz.tuning.reg_free = std::max(d->tuning.reg_free, 0);
+  hda_tuning plain;
+  if (hda_replay_resolve(&dz, &plain) != HDA_OK) return HDA_E_INVAL;
+  const std::vector<hda_tuning> cand = lean_candidates(d->tuning, plain);
   hda_tuning pick;
   int rc = time_candidates(d, off, arena, align, algo, sample, kCut, cand, s, &pick);
   if (rc == HDA_E_INVAL) return hda_replay_resolve(d, out);
