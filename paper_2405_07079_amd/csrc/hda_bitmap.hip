@@ -32,7 +32,8 @@ constexpr int64_t kMaxWaves = 4096;
 // 64) and the first live entries in the same bytes
 constexpr uint32_t kLdsNodes = 64;
 constexpr uint32_t kLdsWaveBytes = 10240;
-// the workspace starts with the heap queue's counter (256 bytes)
+// the workspace starts with the heap queue's counter and the moved heaps'
+// (256 bytes)
 constexpr uint64_t kHeaderBytes = 256;
 
 // Workspace words of one wave's slot: the flags of max_granules, their node
@@ -45,10 +46,11 @@ uint64_t slot_words(uint64_t max_granules, int64_t cap_live) {
 
 int64_t n_waves(int64_t heaps) { return heaps < kMaxWaves ? heaps : kMaxWaves; }
 
-// The queue counter starts at 0 (a kernel rather than a memset, so the pair
-// of launches can be captured in a graph).
+// The queue counter and, after it, the count of heaps that moved to the flags
+// start at 0 (a kernel rather than a memset, so the pair of launches can be
+// captured in a graph).
 __global__ void bitmap_reset(uint32_t* queue) {
-  if (threadIdx.x == 0) *queue = 0u;
+  if (threadIdx.x < 2) queue[threadIdx.x] = 0u;
 }
 
 struct BitmapParams {
@@ -150,6 +152,7 @@ int hda_bitmap_replay(const hda_batch_desc* d, uint64_t max_granules, void* stre
   uintptr_t base = reinterpret_cast<uintptr_t>(d->workspace);
   base = (base + 255u) & ~uintptr_t(255);
   b.ws = reinterpret_cast<uint64_t*>(base);
+  p.migrated = reinterpret_cast<uint32_t*>(base) + 1;
   b.max_granules = max_granules;
   b.words = slot_words(max_granules, d->meta_live);
   b.waves = n_waves(d->n_heaps);

@@ -30,8 +30,9 @@ namespace {
 
 constexpr int kClasses = 2;  // heaps with valid parameters, and the others
 constexpr int kValid = 0, kInvalid = 1;
-// Queue words in the workspace: the heap queue, the number of heaps moved
-// from the lean to the general core, and the queue of the ordered-core launch.
+// Queue words in the workspace: the heap queue, the number of heaps that left
+// the lean core (the tests read it; not kept where every heap has a wave and
+// no classify kernel clears it), and the queue of the heavy launch.
 constexpr int kQueueWords = 3;
 constexpr int kMigrated = 1;
 constexpr int kHeavyQueue = 2;

@@ -31,7 +31,7 @@ struct ReplayParams {
   Ent* spill_free;       // per wave slot: cold free entries past LDS
   uint32_t* spill_stamp; // per wave slot: their stamps
   Ent* spill_live;       // per wave slot: cold live entries past LDS
-  uint32_t* migrated;    // heaps moved from the lean to the general core, or null
+  uint32_t* migrated;    // count of the heaps that left the lean core, or null
   int64_t n_heaps;       // heaps handled by this launch
   int64_t first;         // index into `order` of the first heap
   uint32_t cap_free, cap_live;   // total table capacities per heap

@@ -9,6 +9,7 @@ import tempfile
 import numpy as np
 import pytest
 
+import edge_traces
 import emu
 import oracle
 from paper_2405_07079_amd import workloads as W
@@ -118,3 +119,15 @@ def test_heavy_heaps_that_outgrow_a_small_pool(lib, algo):
         assert np.array_equal(res, want[0]) and np.array_equal(status, want[2])
         assert np.array_equal(states[0], want[1][0])
         assert nxt[0] == ORDERED, f"capacity {cap}: left at request {at[0]}, {free[0]} free"
+
+
+@pytest.mark.parametrize("algo", (0, 1, 2, 3, 4))
+def test_largest_arena_after_the_move(lib, algo):
+    """2^32 - 1 granules: blocks that end at the last granule and whole-arena
+    requests on the ordered core, beside hundreds of small free blocks."""
+    # (TLSF's list heads take 8 KiB of the pool)
+    small, pool = (1400, 10240) if algo == W.TLSF else (500, 2048)
+    b = edge_traces.fragments_then_edges(algo, (1 << 32) - 1, 64, small, 150, seed=algo)
+    res, states, status, nxt, at, free = replay(lib, b, pool, HEAVY)
+    assert nxt[0] == ORDERED and at[0] < 1.5 * small
+    check_oracle(b, res, states, status)

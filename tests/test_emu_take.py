@@ -9,6 +9,7 @@ import tempfile
 import numpy as np
 import pytest
 
+import edge_traces
 import emu
 import oracle
 from paper_2405_07079_amd import workloads as W
@@ -80,3 +81,11 @@ def test_the_move_does_not_read_every_node(lib):
     large = replay(lib, 4096 * NODE, req, 1024, 64, with_state=False)
     assert small[0] == large[0] == 1
     assert abs(large[1] - small[1]) < 4096
+
+
+def test_ragged_arena_on_the_flags(lib):
+    """2^20 - 1 granules after the move: blocks that end at the last granule,
+    in a ragged last word and node."""
+    b = edge_traces.fragments_then_edges(W.BITMAP, (1 << 20) - 1, 16, 300, 120, seed=5)
+    moved, _ = replay(lib, (1 << 20) - 1, b.req, 1024, 64)
+    assert moved == 1
