@@ -4,9 +4,8 @@
 // of the same core as the batched replay, and stores them back.  The result
 // goes straight to the heap's word in pinned host memory, where the caller
 // looks for it: a copy back and a wait for the stream were more than half of
-// a call (22.8 -> 8.2 us for an allocation or a free on a 4 GiB heap).  The
-// word is the kernel's last store, released after the heap's state (0.2 us of
-// the 8.2).
+// a call (22.8 -> 7.9 us for an allocation or a free on a 4 GiB heap).  The
+// word is the kernel's last store, after the heap's state.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
