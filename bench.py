@@ -420,8 +420,9 @@ def leg_c3(W, hda, oracle, torch, stream, cores):
 
 
 def leg_c5(W, hda, oracle, torch, stream):
-    """The 256 GiB segregated-fit heap (4 KiB granules), 50 M requests, on
-    the ordered core (one wavefront with the whole LDS of a workgroup)."""
+    """The 256 GiB segregated-fit heap (4 KiB granules), 50 M requests, in the
+    heavy launch (one wavefront with the whole LDS of a workgroup): the lean
+    core, then the ordered core for nearly all of them."""
     import hashlib
     t0 = time.perf_counter()
     b = W.large_seg_fit()

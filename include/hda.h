@@ -197,8 +197,9 @@ int hda_bitmap_replay(const hda_batch_desc *d, uint64_t max_granules, void *stre
 
 /* Bytes of device scratch for hda_replay on `d` (reads only n_heaps,
  * meta_free, meta_live and tuning).  A smaller workspace is taken as long as
- * it holds the general path's slots (12 instead of 32 bytes per free entry of
- * capacity and heap in flight).  Returns 0 on invalid arguments. */
+ * it holds the general path's slots: 12 instead of 32 bytes per free entry of
+ * capacity and heap in flight, 0.47 instead of 0.81 GB for 4,096 heaps in
+ * flight at the default capacities.  Returns 0 on invalid arguments. */
 size_t hda_replay_workspace(const hda_batch_desc *d);
 
 /* hda_replay for callers that cannot allocate device memory (code under
@@ -207,8 +208,10 @@ size_t hda_replay_workspace(const hda_batch_desc *d);
  * HDA_STATIC_SCRATCH_BYTES that the library holds on every GPU it runs on
  * until the process ends; d->workspace and d->workspace_bytes are ignored.
  * Nothing is allocated or freed (no hipMalloc / hipFree, no allocator
- * callback).  HDA_E_RANGE when hda_replay_workspace(d) exceeds
- * HDA_STATIC_SCRATCH_BYTES (fewer heaps per call, smaller meta_free /
+ * callback).  Where hda_replay_workspace(d) exceeds HDA_STATIC_SCRATCH_BYTES
+ * (some 340 heaps at the default capacities) heaps that outgrow their LDS go
+ * on on the general path; HDA_E_RANGE where its smaller slots do not fit
+ * either (some 580 heaps; fewer heaps per call, smaller meta_free /
  * meta_live, or fewer persistent groups bring it down); HDA_E_INVAL /
  * HDA_E_DEVICE as for hda_replay.  Every call on one GPU uses that GPU's one
  * array, which keeps the last call's contents: calls whose work overlaps on
@@ -241,10 +244,11 @@ int hda_replay_per_heap(const hda_batch_desc *d, void *stream);
  * holds at once), each trace cut to its first 65,536 requests, at most 16 M
  * requests in all.  Candidates: 1, 2, 4, 8 or 16 heaps per workgroup x
  * (lds_free, lds_live) = (64, 512), (128, 1024), (256, 2048), (512, 4096),
- * those that fit the device's LDS; then, with the fastest of those, 0, 16,
- * 64 or 128 heaps (the longest) on the ordered core (heavy_heaps, 64 KiB
- * pools), timed on the 128 longest heaps with traces cut to 1 M requests
- * (not tried when meta_free exceeds the 4,096 free blocks that core holds).
+ * those that fit the device's LDS, and the batch's default plan; then, with
+ * the fastest of those, 0, 16, 64 or 128 heaps (the longest) in the launch of
+ * their own (heavy_heaps, 64 KiB pools), timed on the 128 longest heaps with
+ * traces cut to 1 M requests (not tried when meta_free exceeds the 4,096 free
+ * blocks that the ordered core holds).
  * A later call on a batch of the same shape on the same device (heap count,
  * capacities, sample_heaps, reg_free, and every heap's trace length, arena,
  * alignment and algorithm) returns the earlier choice without timing.  The

@@ -8,8 +8,9 @@
 // the vector instructions that keep the summaries (120 per request); the
 // table's answer is one test of the block at the rover, or one scan of a few
 // 64-entry chunks: 4,096 heaps of 16 MiB at 64 B, 40,000 requests each, in
-// 20.2 ms against 51.0 ms on the flags (26.1 ms when the table took over).  Heaps whose blocks outgrow the share (sizes to 1/256 of the
-// arena) still gain 1.2x from the part before the move.
+// 19.9 ms against 51.0 ms on the flags.  Heaps that move after a quarter of
+// their trace (1,024 heaps, 20,000 requests, blocks to 4 or 16 KiB) still gain
+// 1.13x from the part before, and 4,096 of them 1.14x.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>

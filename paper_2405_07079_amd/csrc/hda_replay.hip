@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(1024) general_kernel(ReplayParams p) {
 // own: each is compiled by itself, so that the lean request loops do not
 // share a register budget with the ordered and general cores (all in one
 // function they took the kernel past 128 VGPRs and into scratch in the loops;
-// calls from within the lean part cost the loops 2-3 %).  The calls are three
+// calls from within the lean part cost the loops 2-3 %).  The calls are two
 // per heap at most.  Arguments are wave-uniform but for LeanExit::cnt; the
 // kernel's parameters are read from where the launch put them.
 typedef const __attribute__((address_space(4))) ReplayParams* LaunchParams;
@@ -336,7 +336,7 @@ struct Plan {
   bool ord_spill = false;  // heaps that outgrow the lean pool go to the ordered core
   uint32_t capF, capL;
   Pass main;
-  // the ordered-core launch: the first `heavy` heaps of the order, one wave
+  // the heavy launch: the first `heavy` heaps of the order, one wave
   // per workgroup with a pool of heavy_pool LDS bytes, heavy_groups of them
   int64_t heavy = 0;
   uint32_t heavy_pool = 0;
@@ -380,7 +380,7 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl, bool may_ord 
   const bool lean = rf > 0;
   const uint32_t capF = round64(d->meta_free > 0 ? d->meta_free : 4096);
   const uint32_t capL = round64(d->meta_live > 0 ? d->meta_live : 8192);
-  // the ordered-core launch (persistent replays only)
+  // the heavy launch (persistent replays only)
   const int64_t heavy = persistent ? std::min<int64_t>(tu.heavy_heaps, d->n_heaps) : 0;
   int heavy_cus = 0;
   if (heavy > 0) {
@@ -398,7 +398,7 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl, bool may_ord 
     heavy_cus = (int)((pl->heavy_groups + nb - 1) / nb);
     pl->heavy_stride = (ord_spill_bytes(capF, capL) + 255) / 256 * 256;
   }
-  // the other heaps fill the CUs the ordered-core launch leaves
+  // the other heaps fill the CUs the heavy launch leaves
   const int light_cus = std::max(1, dc->cus - heavy_cus);
   // Lean launches of few heaps run one or two to a workgroup, spread over the
   // CUs, and get a larger pool each: 60, 40 or 20 KiB, within the 64 KiB a
@@ -429,7 +429,8 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl, bool may_ord 
   if (lean) {
     // one LDS pool per wave with room for want_kf segregated-fit free
     // entries (16 B) and want_kl live entries (8 B); a heap that outgrows it
-    // continues on the general core in its device-memory slot
+    // continues in its device-memory slot, on the ordered core if that holds
+    // its slots (ord_spill), else on the general core
     m.kf = m.kl = 0;
     m.sf = capF;
     m.sl = capL;
@@ -468,7 +469,7 @@ bool make_plan(const hda_batch_desc* d, bool persistent, Plan* pl, bool may_ord 
   m.groups = persistent ? occupancy_groups(set->fn, W, m.lds_group, light_cus, tu.groups,
                                            d->n_heaps - heavy)
                         : 1;
-  // (no slots where the ordered-core launch takes every heap)
+  // (no slots where the heavy launch takes every heap)
   m.slots = heavy > 0 && heavy == d->n_heaps ? 0 : m.groups * W;
   pl->set = set;
   pl->lean = lean;
@@ -559,7 +560,7 @@ ReplayParams replay_params(const hda_batch_desc* d, const Plan& pl) {
   return p;
 }
 
-// Parameters of the ordered-core launch: list positions [0, heavy), its own
+// Parameters of the heavy launch: list positions [0, heavy), its own
 // queue counter, its device slots.
 ReplayParams heavy_params(const hda_batch_desc* d, const Plan& pl) {
   ReplayParams p = replay_params(d, pl);
@@ -590,7 +591,7 @@ bool set_lds_attrs(const Plan& pl) {
 }
 
 // A second stream per device for the launch that runs beside the
-// ordered-core one (default priority, not blocking the null stream).
+// heavy one (default priority, not blocking the null stream).
 hipStream_t fork_stream() {
   static std::mutex mu;
   static std::vector<hipStream_t> streams;
@@ -616,9 +617,9 @@ int classify(const hda_batch_desc* d, const Plan& pl, hipStream_t s) {
 }
 
 // The replay kernel alone when every heap has a wave of its own; else
-// classify, then the persistent replay kernel, both on s.  With heaps for
-// the ordered core, their launch follows classify on s and the other heaps'
-// launch runs beside it on the fork stream, joined back to s by an event.
+// classify, then the persistent replay kernel, both on s.  With heavy heaps,
+// their launch follows classify on s and the other heaps' launch runs beside
+// it on the fork stream, joined back to s by an event.
 int enqueue(const hda_batch_desc* d, const Plan& pl, hipStream_t s) {
   ReplayParams p = replay_params(d, pl);
   const dim3 grid((uint32_t)pl.main.groups), block(64 * pl.main.W);
@@ -939,11 +940,12 @@ int hda_replay_autotune(const hda_batch_desc* d, int32_t sample_heaps, void* str
   int rc = time_candidates(d, off, arena, align, algo, sample, kCut, cand, s, &pick);
   if (rc == HDA_E_INVAL) return hda_replay_resolve(d, out);
   if (rc != HDA_OK) return rc;
-  // 2. how many of the longest heaps the ordered core takes (0, 16, 64,
+  // 2. how many of the longest heaps the heavy launch takes (0, 16, 64,
   // 128, or every sampled heap when fewer), timed on the 128 longest heaps
   // with traces up to kHeavyCut requests, so that their tables reach the
-  // sizes that set the makespan.  The ordered core holds at most
-  // kOrdMaxFree free blocks: with larger meta_free it is not tried.
+  // sizes that set the makespan.  The ordered core, which its heaps move to,
+  // holds at most kOrdMaxFree free blocks: with larger meta_free it is not
+  // tried.
   if (d->meta_free <= (int64_t)kOrdMaxFree) {
     const std::vector<int32_t> longest = longest_heaps(off, 128, 1, kBudget, kHeavyCut);
     const int64_t S2 = (int64_t)longest.size();

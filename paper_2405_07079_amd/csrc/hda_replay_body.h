@@ -132,7 +132,8 @@ __device__ __forceinline__ uint32_t run_block(Core& w, uint32_t n, uint32_t w0, 
   }
   for (uint32_t j = 0; j < n; ++j, frees >>= 1) {
     const uint32_t v0 = rdlane(w0, j);
-    // (past the block's end: no request, nothing is loaded)
+    // (past the end of a last, shorter block the lanes hold copies of the last
+    // request: what is loaded for them is in bounds and not used)
     if constexpr (UNCHK && LooksAhead<Core>::value)
       w.next_request(keep_scalar((uint32_t)frees) & 2u, rdlane(w0, j + 1u));
     int64_t r;
@@ -283,18 +284,6 @@ __device__ __forceinline__ void reject_heap(const ReplayParams& p, int64_t heap)
   }
 }
 
-// Replay one heap known to use algorithm ALGO (its parameters are checked
-// again; a heap that fails the check is rejected).
-template <int ALGO, int RF, int RL>
-__device__ __forceinline__ void replay_one_heap(const ReplayParams& p, const Cold& c, int64_t heap) {
-  HeapRegs h;
-  if (!heap_params(p, heap, h) || h.algo != ALGO) {
-    reject_heap(p, heap);
-    return;
-  }
-  replay_heap<ALGO, RF, RL>(p, c, h, heap);
-}
-
 // Lean path (hda_lean.h).  A heap whose tables outgrow the lean pool goes on
 // from the request that did not fit: on the ordered core (hda_ordered.h) in
 // the same LDS and the wave's device slot `ord`, where every request costs
@@ -318,10 +307,10 @@ struct LeanExit {
 // ordered core, whose request costs the same at any size, than scanning them
 // 64 at a time.  Where the two cross, with pools of 20 KiB or more (at most
 // two waves a SIMD): 500 first-fit heaps 9.4 ms without a limit, 7.9 / 7.3 /
-// 7.0 ms at 512 / 384 / 256; 1,000 next-fit heaps 6.1 ms, 5.3 / 5.2 / 5.3;
-// 200 segregated-fit heaps 20.6 ms, 16.7 / 16.8 / 17.1; one best-fit heap
-// (two sorted tables on the ordered core) 12.7 ms, 13.2 / 14.3 / 15.3.  With
-// four waves a SIMD the pools end before it matters (11.04 ms either way).
+// 7.0 ms at 512 / 384 / 256; 1,000 next-fit heaps in 40 KiB pools 6.1 ms, 5.3 /
+// 5.2 / 5.3; 200 segregated-fit heaps 20.6 ms, 16.7 / 16.8 / 17.1; one best-fit
+// heap (two sorted tables on the ordered core) 12.7 ms, 13.2 / 14.3 / 15.3.
+// Pools of 10 KiB end before it matters (11.04 ms either way).
 __device__ __forceinline__ constexpr uint32_t lean_max_free(int algo) {
   return algo == kFirstFit ? 256u : algo == kNextFit ? 384u : algo == kBestFit ? 1024u : 512u;
 }
