@@ -56,16 +56,13 @@ __device__ inline void store_regs(HeapHdr* hd, const HeapRegs& h) {
 enum : int { kOpInit = 0, kOpAlloc = 1, kOpFree = 2, kOpDump = 3, kOpFreePartial = 4 };
 
 // The caller's host thread returns as soon as it sees `r` in *word, so the
-// heap's tables and registers are stored first and their stores have completed
-// in device memory's cache before the word goes out: a call that has returned
-// has nothing left to do on the device but end its kernel.  (Whoever reads the
-// heap next -- another call, a copy -- is ordered on the same stream after the
-// kernel's end, which makes the stores visible beyond this XCD; releasing the
-// word at system scope would write that cache back a second time, 0.3 us of an
-// 8 us call.)
+// heap's tables and registers are stored first and the word is released at
+// system scope after them: a call that has returned has nothing left to do on
+// the device but end its kernel, not even to write the heap's lines back, and
+// its memory may be given to others without a wait for the stream.
 __device__ inline void publish(int64_t* word, int64_t r) {
-  stores_done();
-  if (lane_id() == 0) __hip_atomic_store(word, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  wave_sync();  // (every lane has stored its part)
+  if (lane_id() == 0) __hip_atomic_store(word, r, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 template <int ALGO>

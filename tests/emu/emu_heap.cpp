@@ -10,10 +10,10 @@
 #include "emu_wave.h"
 
 namespace {
-void emu_publish(int64_t* word, int64_t r);
+void emu_publish(int64_t* word, int64_t r, bool release);
 }
 #define __HIP_MEMORY_SCOPE_SYSTEM 0
-#define __hip_atomic_store(p, v, order, scope) emu_publish(p, v)
+#define __hip_atomic_store(p, v, order, scope) emu_publish(p, v, (order) == __ATOMIC_RELEASE)
 
 #include "hda_core.h"
 #include "hda_heap_dev.h"
@@ -35,13 +35,15 @@ struct CallJob {
   int64_t cap;
   int64_t* word;
   std::vector<uint8_t>* seen;  // the heap's bytes as published
+  bool released;
   int done;
 };
 CallJob g_call;
 
-void emu_publish(int64_t* word, int64_t r) {
+void emu_publish(int64_t* word, int64_t r, bool release) {
   const uint8_t* b = reinterpret_cast<const uint8_t*>(g_call.hd);
   g_call.seen->assign(b, b + heap_bytes(g_call.hd->cf, g_call.hd->cl));
+  g_call.released = release;
   *word = r;
 }
 
@@ -70,7 +72,7 @@ void call_main() {
 
 // Run n calls (op[i], arg[i]) on a new heap of `cap` entries per table.
 // res[i] is the published result; early[i] = 1 if it was published before the
-// heap's memory was as the call left it.
+// heap's memory was as the call left it, or not as a release.
 extern "C" int emu_heap_calls(int algo, int64_t arena, int64_t align, uint32_t cap, int64_t n,
                               const int32_t* op, const int64_t* arg, int64_t* res,
                               uint8_t* early) {
@@ -91,7 +93,7 @@ extern "C" int emu_heap_calls(int algo, int64_t arena, int64_t align, uint32_t c
   for (int64_t i = -1; i < n; ++i) {  // (-1: the heap's first call)
     int64_t word = INT64_MIN;
     g_call = CallJob{hd, i < 0 ? (int)kOpInit : op[i], i < 0 ? 0 : arg[i], dump.data(),
-                     (int64_t)dump.size(), &word, &seen, 0};
+                     (int64_t)dump.size(), &word, &seen, false, 0};
     for (int l = 0; l < 64; ++l) {
       getcontext(&w.lane_ctx[l]);
       w.lane_ctx[l].uc_stack.ss_sp = stacks[l].data();
@@ -103,7 +105,7 @@ extern "C" int emu_heap_calls(int algo, int64_t arena, int64_t align, uint32_t c
     swapcontext(&w.main_ctx, &w.lane_ctx[0]);
     if (i < 0) continue;
     res[i] = word;
-    early[i] = seen.size() != heap_bytes(cap, cap) ||
+    early[i] = !g_call.released || seen.size() != heap_bytes(cap, cap) ||
                std::memcmp(seen.data(), hd, seen.size()) != 0;
   }
   emu_wave = nullptr;

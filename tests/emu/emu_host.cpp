@@ -17,9 +17,11 @@ uint32_t emu_lane = 0;
 
 void (*emu_on_host_free)() = nullptr;
 int emu_host_pages = 0;
+int emu_stream_waits = 0;
 
 extern "C" void emu_set_on_host_free(void (*f)()) { emu_on_host_free = f; }
 extern "C" int emu_pages() { return emu_host_pages; }
+extern "C" int emu_waits() { return emu_stream_waits; }
 
 namespace {
 

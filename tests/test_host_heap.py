@@ -118,3 +118,15 @@ def test_a_page_is_freed_outside_the_pools_lock(lib):
             t.join(20)
         for h in done:
             assert lib.hda_heap_destroy(h) == 0
+
+
+def test_an_idle_heap_goes_without_a_wait_for_its_stream(lib):
+    """Calls return when their result is released, after everything else they
+    store: giving up the heap has nothing to wait for, where a wait would stand
+    behind whatever kernel shares the stream's hardware queue."""
+    h = create(lib)
+    assert lib.hda_alloc(h, ctypes.c_uint64(64)) == 0
+    assert lib.hda_free(h, ctypes.c_int64(0)) == 0
+    waits = lib.emu_waits()
+    assert lib.hda_heap_destroy(h) == 0
+    assert lib.emu_waits() == waits
