@@ -187,10 +187,12 @@ int call(hda_heap* h, int op, int64_t arg, int64_t* result, int64_t* dump, size_
   if (op == kOpDump) {
     *len = (size_t)r;
     if ((size_t)r > cap) return HDA_E_RANGE;
+    h->pending = true;
     if (r > 0 && (hipMemcpyAsync(dump, h->io, (size_t)r * 8, hipMemcpyDeviceToHost, h->stream) !=
                       hipSuccess ||
                   hipStreamSynchronize(h->stream) != hipSuccess))
       return HDA_E_DEVICE;
+    h->pending = false;
     return HDA_OK;
   }
   *result = r;
@@ -424,10 +426,12 @@ int hda_heap_load(hda_heap* h, const int64_t* buf, size_t len) {
   const int rc = build_image(h, buf, len, img);
   if (rc != HDA_OK) return rc;
   std::lock_guard<std::mutex> g(h->mu);
+  h->pending = true;
   if (hipMemcpyAsync(h->dev, img.data(), img.size(), hipMemcpyHostToDevice, h->stream) !=
           hipSuccess ||
       hipStreamSynchronize(h->stream) != hipSuccess)
     return HDA_E_DEVICE;
+  h->pending = false;
   return HDA_OK;
 }
 
